@@ -31,6 +31,20 @@ struct bs_pattern_s {
   // pos(k,j) << 16 | pos(i,j) per entry (i,j), j > k, that row k holds
   // (positions in the pattern's CSR order)
   std::vector<int> ilu_ptr, ilu_ops;
+  // ILU(0) schedule of the one-wave factorization (patterns of up to 64 rows;
+  // F is the factor array, row-major with stride ilu_stride(n)): for each pivot
+  // k that a later row holds, in increasing order, its columns j > k that such
+  // a row holds too, four per record of 16 words:
+  //   0..7   per column, the rows i > k that hold both k and j (64 bits each,
+  //          none past the pivot's last column)
+  //   8..11  per column, its byte offset in a row (that of k past the last)
+  //   12, 13 the rows i > k that hold k
+  //   14     byte offset of column k, bit 31 on the pivot's first record
+  //   15     byte offset of row k
+  // Empty records make their number a multiple of three, and two more are read
+  // ahead.
+  std::vector<int> ilu64;
+  int ilu64_records = 0;
   // Sweep lists of the multi-wave teams (ILU(0) substitutions, BatchTrsv):
   // rows by lower level | rows by upper level | lower level starts (nlev_l+1)
   // | upper level starts (nlev_u+1) | per row its list start (16 bits),
@@ -41,8 +55,8 @@ struct bs_pattern_s {
   // bank-aware layout for one-wave teams of layout_nz register slots (0: none)
   std::vector<int> layout;
   int layout_nz = 0;
-  // one allocation: row_ptr | slot_col | row_len | diag_slot | lev | ilu_ptr |
-  // ilu_ops | sweep | layout
+  // one allocation: ilu64 | row_ptr | slot_col | row_len | diag_slot | lev |
+  // ilu_ptr | ilu_ops | sweep | layout
   int* d_base = nullptr;
   int *d_row_ptr = nullptr, *d_slot_col = nullptr, *d_row_len = nullptr, *d_diag = nullptr;
   int *d_lev = nullptr, *d_ilu_ptr = nullptr, *d_ilu_ops = nullptr, *d_sweep = nullptr;
@@ -158,6 +172,41 @@ void derive(bs_pattern_s& p) {
       p.ilu_ptr[i + 1] = (int)p.ilu_ops.size();
     }
   }
+  // The one-wave schedule: rows and columns as 64-bit masks.
+  p.ilu64.clear();
+  if (n <= bs::kWave) {
+    std::vector<uint64_t> row(n, 0), col(n, 0);
+    for (int i = 0; i < n; ++i)
+      for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) {
+        row[i] |= 1ull << p.col[e];
+        col[p.col[e]] |= 1ull << i;
+      }
+    const int stride = bs::ilu_stride(n) * 8;
+    for (int k = 0; k + 1 < n; ++k) {
+      const uint64_t later = (~0ull << k) << 1, below = col[k] & later;
+      if (!below) continue;
+      std::vector<int> js;
+      for (int j = k + 1; j < n; ++j)
+        if ((row[k] >> j & 1) && (col[j] & below)) js.push_back(j);
+      for (size_t at = 0; at == 0 || at < js.size(); at += 4) {
+        unsigned w[16] = {0};
+        for (int q = 0; q < 4; ++q) {
+          const bool has = at + q < js.size();
+          const uint64_t rows = has ? col[js[at + q]] & below : 0;
+          w[2 * q] = (unsigned)rows;
+          w[2 * q + 1] = (unsigned)(rows >> 32);
+          w[8 + q] = (unsigned)(has ? js[at + q] : k) * 8;
+        }
+        w[12] = (unsigned)below;
+        w[13] = (unsigned)(below >> 32);
+        w[14] = (unsigned)(k * 8) | (at == 0 ? 1u << 31 : 0u);
+        w[15] = (unsigned)(k * stride);
+        for (unsigned v : w) p.ilu64.push_back((int)v);
+      }
+    }
+    p.ilu64_records = (int)(p.ilu64.size() / 16 + 2) / 3 * 3;
+    p.ilu64.resize((size_t)(p.ilu64_records + 2) * 16, 0);
+  }
   // Sweep lists (same 15-bit positions; rows of up to 255 entries per triangle;
   // columns below 2^15).
   p.sweep.clear();
@@ -217,10 +266,12 @@ int upload(bs_pattern_s& p) {
   const size_t n_rp = p.n + 1, n_sc = std::max<size_t>((size_t)p.width * p.n, 1), n_rl = p.n;
   const size_t n_ops = std::max<size_t>(p.ilu_ops.size(), 1);
   const size_t n_sw = std::max<size_t>(p.sweep.size(), 1);
-  const size_t total = n_rp + n_sc + 3 * n_rl + n_rp + n_ops + n_sw + p.layout.size();
+  // (ilu64 first: its 64-byte records are aligned to their size)
+  const size_t n_i64 = p.ilu64.size();
+  const size_t total = n_i64 + n_rp + n_sc + 3 * n_rl + n_rp + n_ops + n_sw + p.layout.size();
   e = hipMalloc(&p.d_base, total * sizeof(int));
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(pattern)");
-  p.d_row_ptr = p.d_base;
+  p.d_row_ptr = p.d_base + n_i64;
   p.d_slot_col = p.d_row_ptr + n_rp;
   p.d_row_len = p.d_slot_col + n_sc;
   p.d_diag = p.d_row_len + n_rl;
@@ -230,16 +281,18 @@ int upload(bs_pattern_s& p) {
   p.d_sweep = p.d_ilu_ops + n_ops;
   p.d_layout = p.layout.empty() ? nullptr : p.d_sweep + n_sw;
   std::vector<int> h(total, -1);
+  const auto at = h.begin() + n_i64;
+  std::copy(p.ilu64.begin(), p.ilu64.end(), h.begin());
   const size_t o_lev = n_rp + n_sc + 2 * n_rl, o_ptr = o_lev + n_rl, o_ops = o_ptr + n_rp;
-  std::copy(p.lev.begin(), p.lev.end(), h.begin() + o_lev);
-  std::copy(p.ilu_ptr.begin(), p.ilu_ptr.end(), h.begin() + o_ptr);
-  std::copy(p.ilu_ops.begin(), p.ilu_ops.end(), h.begin() + o_ops);
-  std::copy(p.sweep.begin(), p.sweep.end(), h.begin() + o_ops + n_ops);
-  std::copy(p.layout.begin(), p.layout.end(), h.begin() + o_ops + n_ops + n_sw);
-  std::copy(p.row_ptr.begin(), p.row_ptr.end(), h.begin());
-  std::copy(p.slot_col.begin(), p.slot_col.end(), h.begin() + n_rp);
-  std::copy(p.row_len.begin(), p.row_len.end(), h.begin() + n_rp + n_sc);
-  std::copy(p.diag_slot.begin(), p.diag_slot.end(), h.begin() + n_rp + n_sc + n_rl);
+  std::copy(p.lev.begin(), p.lev.end(), at + o_lev);
+  std::copy(p.ilu_ptr.begin(), p.ilu_ptr.end(), at + o_ptr);
+  std::copy(p.ilu_ops.begin(), p.ilu_ops.end(), at + o_ops);
+  std::copy(p.sweep.begin(), p.sweep.end(), at + o_ops + n_ops);
+  std::copy(p.layout.begin(), p.layout.end(), at + o_ops + n_ops + n_sw);
+  std::copy(p.row_ptr.begin(), p.row_ptr.end(), at);
+  std::copy(p.slot_col.begin(), p.slot_col.end(), at + n_rp);
+  std::copy(p.row_len.begin(), p.row_len.end(), at + n_rp + n_sc);
+  std::copy(p.diag_slot.begin(), p.diag_slot.end(), at + n_rp + n_sc + n_rl);
   e = hipMemcpy(p.d_base, h.data(), total * sizeof(int), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(p.d_base);
@@ -420,7 +473,7 @@ int make_plan(bs_format fmt, int n, int nnz, int max_row, int width, bs_solver s
   const int stored = fmt == BS_CSR ? nnz : width * n;
   const bool mixed = variant == bs::V_GMRES_MIXED;
   const int vec = teams * (bs::team_vec_bytes(rows, gm, wg, mixed) + bs::bj_bytes(rows, block) +
-                           (tri ? bs::tri_region_bytes(team, n, nnz) : 0)) +
+                           (tri ? bs::tri_region_bytes(team, n, nnz, trsv) : 0)) +
                   bs::red_lds_bytes(waves);
   int stage = 0;
   // ILU(0) and the triangular solves are bound by their substitution chains,
@@ -791,11 +844,20 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
     a.block = block;
     a.bj_offset = a.team_bytes;
     a.team_bytes += bs::bj_bytes(rows, block) +
-                    (ilu || trsv ? bs::tri_region_bytes(pl.info.team, pattern->n, pattern->nnz)
+                    (ilu || trsv ? bs::tri_region_bytes(pl.info.team, pattern->n, pattern->nnz, trsv)
                                  : 0);
     a.stage_vals_bytes = bs::stage_vals_bytes(teams, stored, pl.info.slots);
     a.stage_team_bytes = a.stage_vals_bytes + bs::stage_b_bytes(teams, pattern->n);
     a.stage_offset = teams * a.team_bytes + bs::red_lds_bytes(waves);
+    // One-wave ILU(0) (BiCGSTAB) and BatchTrsv: the next system's values travel
+    // in registers during a solve and pass through the region of the factors
+    // or the triangle, which the solve no longer needs by then; where the
+    // block is longer than the registers kept for it, or than the region, the
+    // rows are read straight from memory.
+    if ((ilu || trsv) && solver != BS_GMRES && pl.info.team == bs::kWave &&
+        a.stage_vals_bytes <= bs::pf_chunks(pl.info.slots) * 1024 &&
+        a.stage_vals_bytes + bs::round16(pattern->n * 8) + 16 <= a.team_bytes - a.bj_offset)
+      a.stage = 3;
     // CSR rows go through a fixed window when the block holds a full window
     a.window = (fmt == BS_CSR && pattern->nnz >= pl.info.slots) ? 1 : 0;
   }
@@ -810,6 +872,8 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   a.nlev_u = pattern->nlev_u;
   a.ilu_ptr = pattern->d_ilu_ptr;
   a.ilu_ops = pattern->d_ilu_ops;
+  a.ilu64 = pattern->d_base;
+  a.ilu64_records = pattern->ilu64_records;
   a.sweep = pattern->d_sweep;
   a.sweep_ents = pattern->sweep_ents;
   a.values = values;

@@ -200,6 +200,9 @@ __device__ __forceinline__ void lds_store(unsigned addr, T v) {
   *(__attribute__((address_space(3))) T*)(lds_char*)(uintptr_t)addr = v;
 }
 
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+typedef unsigned uint16v __attribute__((ext_vector_type(16)));
+
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
@@ -229,7 +232,7 @@ struct Team {
     live = false;
     lds = smem + (size_t)tix * a.team_bytes;
     stage_all = smem + a.stage_offset;
-    stage = stage_all + (size_t)tix * a.stage_team_bytes;
+    stage = a.stage == 3 ? lds + a.bj_offset : stage_all + (size_t)tix * a.stage_team_bytes;
     red = reinterpret_cast<double*>(smem + (size_t)S::TEAMS * a.team_bytes);
     phase = 0;
     lists = false;
@@ -300,6 +303,14 @@ struct Team {
   // wave sees the same (team-uniform) predicate.
   __device__ __forceinline__ bool any(bool p) const { return wave_any(p); }
 
+};
+
+// A system's values and right-hand side on their way through the registers of a
+// wave: 16 bytes per lane of each of the first C KiB, and this lane's b.
+template <int C>
+struct RegBlock {
+  uint4v v[C > 0 ? C : 1];
+  double b;
 };
 
 // ---------------------------------------------------------------- sparse rows
@@ -450,6 +461,37 @@ struct Rows {
         dma16((const void*)src, lds_addr(tm.stage_all + d0));
       }
     }
+  }
+
+  // One-wave teams: load the block of system `sys` (as the 16-byte-aligned
+  // chunks that overlap it) and this lane's b into registers, with every load
+  // in flight; nothing waits for them before put_regs().
+  template <int C>
+  __device__ __forceinline__ void prefetch_regs(const Team<S>& tm, const KArgs& g, int64_t sys,
+                                                RegBlock<C>& p) const {
+    const int64_t per = g.fmt == 0 ? (int64_t)g.nnz : (int64_t)g.width * g.n;
+    const uintptr_t v0 = (uintptr_t)(g.values + matrix_of(g, sys) * per);
+    const uintptr_t va = v0 & ~(uintptr_t)15;
+    const unsigned vlast = (unsigned)(((v0 + (uintptr_t)per * 8 - 1) & ~(uintptr_t)15) - va);
+    const unsigned l16 = 16u * (unsigned)lane_id();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (c * 1024 < g.stage_vals_bytes)
+        p.v[c] = __builtin_nontemporal_load((const uint4v*)(va + min(c * 1024u + l16, vlast)));
+    p.b = g.b[sys * g.n + (ok[0] ? row[0] : 0)];
+  }
+
+  // ... and into the team's staging block, where load_values() reads them.
+  template <int C>
+  __device__ __forceinline__ void put_regs(const Team<S>& tm, const KArgs& g, const RegBlock<C>& p) const {
+    const unsigned st = lds_addr(tm.stage), l16 = 16u * (unsigned)lane_id();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (c * 1024 < g.stage_vals_bytes) lds_store<uint4v>(st + c * 1024 + l16, p.v[c]);
+    const unsigned sb = st + g.stage_vals_bytes + (unsigned)((uintptr_t)(g.b + tm.row0) & 15);
+    if (ok[0]) lds_store<double>(sb + row[0] * 8, p.b);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
   }
 
   // Multi-wave teams (one team per group), CSR: prefetch the values of

@@ -25,7 +25,9 @@ struct KArgs {
   int64_t n_batch;
   int n, nnz, width, fmt;      // fmt: 0 CSR, 1 ELL
   int precond, flags, max_iter, restart;
-  int stage;                   // values and b prefetched into LDS (single-wave groups)
+  int stage;                   // values prefetched: 1 with b into LDS (single-wave groups),
+                               // 2 into LDS by a multi-wave group, 3 into registers
+                               // (one-wave ILU(0) and BatchTrsv), 0 not at all
   int gmres;                   // GMRES scalars live behind the vector buffers
   int team_bytes;              // LDS bytes per team for vectors and scalars
   int stage_team_bytes;        // LDS staging bytes per team (values then b)
@@ -56,6 +58,8 @@ struct KArgs {
   int nlev_l, nlev_u;          // level counts of the lower and upper triangles
   const int* ilu_ptr;          // [n+1] start of each row's ILU(0) steps in ilu_ops
   const int* ilu_ops;          // ILU(0) schedule (header and update words, see the pattern)
+  const int* ilu64;            // ILU(0) records of one-wave teams (see the pattern)
+  int ilu64_records;
   const int* sweep;            // sweep lists of multi-wave teams (see the pattern)
   int sweep_ents;              // entries in those lists
 };
@@ -78,9 +82,19 @@ __host__ __device__ constexpr int bj_bytes(int rows, int block) {
 constexpr int kPkScalar = 0, kPkBlock = 1, kPkIlu = 2;
 
 // ILU(0) of a one-wave team: the factors as an n-row FP64 array, row-major,
-// columns padded with zeros to a multiple of 8 plus one (an odd stride).
+// columns padded with zeros to a multiple of 8 plus one (an odd stride), and
+// eight doubles more that a sweep reads ahead.
 __host__ __device__ constexpr int ilu_stride(int n) { return ((n + 7) & ~7) + 1; }
-__host__ __device__ constexpr int ilu_bytes(int n) { return ((n * ilu_stride(n) * 8) + 15) & ~15; }
+__host__ __device__ constexpr int ilu_bytes(int n) { return ((n * ilu_stride(n) + 8) * 8 + 15) & ~15; }
+
+// BatchTrsv of a one-wave team: the triangle packed by rows, n(n+1)/2 doubles,
+// and what the sweep's last group and its reading ahead take past the end.
+__host__ __device__ constexpr int trsv_bytes(int n) { return ((n * (n + 1) / 2 + 16) * 8 + 15) & ~15; }
+
+// ILU(0) and BatchTrsv on one-wave teams: KiB of a system's values a wave keeps
+// in registers while it solves the system before (16 bytes per lane and KiB).
+// Shapes beyond 32 slots have no registers left for them.
+__host__ __device__ constexpr int pf_chunks(int nz) { return nz <= 28 ? 12 : nz <= 32 ? 10 : 0; }
 
 // Flag bit of the absolute stop criterion (BS_FLAG_ABS_TOL).
 constexpr int kFlagAbsTol = 4;
@@ -193,10 +207,10 @@ __host__ __device__ constexpr IluMw ilu_mw_layout(int n, int nnz) {
   return IluMw{0, y, d, rng, ent, rows, lvl, lvl + round16((2 * n + 2) * 2)};
 }
 
-// LDS bytes of a team's ILU(0) or BatchTrsv region: the dense factors of a
-// one-wave team, the sparse layout above for larger teams.
-__host__ __device__ constexpr int tri_region_bytes(int team, int n, int nnz) {
-  return team <= kWave ? ilu_bytes(n) : ilu_mw_layout(n, nnz).bytes;
+// LDS bytes of a team's ILU(0) or BatchTrsv region: the dense factors or the
+// packed triangle of a one-wave team, the sparse layout above for larger teams.
+__host__ __device__ constexpr int tri_region_bytes(int team, int n, int nnz, bool trsv) {
+  return team > kWave ? ilu_mw_layout(n, nnz).bytes : trsv ? trsv_bytes(n) : ilu_bytes(n);
 }
 
 }  // namespace bs

@@ -210,136 +210,214 @@ __device__ __forceinline__ uint64_t rdlane64(uint64_t v, int l) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// Lanes past lane k (all 64-bit shifts stay below 64).
+__device__ __forceinline__ uint64_t lanes_past(int k) { return (~0ull << k) << 1; }
+
 // Factorization (Saad 2003, Sec. 10.3.2), right-looking: for pivot k, every row
 // i > k that holds column k replaces that entry by l_ik = a_ik / u_kk (a
 // division, as the IKJ form writes it) and subtracts l_ik u_kj from each of
-// its entries j > k; row k's pattern (a wave-uniform bitmask read from lane k)
-// bounds the columns visited, eight per batch of loads, and a row's own
-// pattern mask selects which of them change, so nothing fills in (the others
-// are stored back unchanged).  Each entry receives its updates in increasing
-// k, as in the IKJ form.  d gets the pivot u_ii (1 on idle lanes), which the
-// backward sweep divides by.  A zero pivot or a non-finite factor entry
-// anywhere in the system turns M into the identity (F zero, d = 1).
+// its entries j > k.  The pattern's schedule lists the pivots' columns, four
+// per record, each with the rows that hold it below the pivot: a record comes
+// through the scalar cache while the one before it is worked on, so a column
+// costs its two reads, its update and its store (the lanes that do not hold
+// it store to their own cell of a vector buffer, which nothing reads before it
+// is written again).  Finding the columns and their rows from bit masks here
+// took about 25 instructions per column, most of them one scalar chain: 0.79
+// against 0.44 ms for loading and factoring 16384 systems of 54 rows.  What is
+// left is the LDS: three operations of a whole wave per column, about 80 % of
+// the LDS cycles of this phase; reading the pivot row once and its entries out
+// of the lanes takes a third of them away and is slower (0.49 ms).  Each entry
+// receives its updates in increasing k, as in the IKJ form.  d gets the pivot
+// u_ii (1 on idle lanes), which the backward sweep divides by.  A zero pivot
+// or a non-finite factor entry anywhere in the system turns M into the
+// identity (F zero, d = 1).
 template <class TM, class RW>
 __device__ void ilu_setup(TM& tm, RW& A, const KArgs& g, double (&d)[RW::R]) {
   static_assert(RW::R == 1 && RW::TEAM == kWave, "ILU(0) runs on one-wave teams");
-  constexpr int kB = 8;
   const int n = g.n, st = ilu_stride(n);
-  double* F = tm.bj_region(g);
+  const unsigned F = lds_addr(tm.bj_region(g));
   const int lane = tm.lane;
   const bool ok = A.ok[0];
   const int i = ok ? A.row[0] : 0;  // rows past n address row 0 and never store
-  for (int e = lane; e < n * st; e += kWave) F[e] = 0.0;
-  // columns of the register slots: gather a vector holding each row's index
-  if (ok) lds_store<double>(A.vrow[0] + RW::kBuf, (double)i);
-  tm.sync();
-  uint64_t mask = 0;
+  const unsigned fi = F + (unsigned)(i * st) * 8, spare = A.vrow[0];
+  auto clear = [&]() {
+    for (unsigned e = 16u * (unsigned)lane; e < (unsigned)ilu_bytes(n); e += 16u * kWave)
+      lds_store<uint4v>(F + e, uint4v{0, 0, 0, 0});
+  };
+  clear();
+  wave_lds_fence();
+  // slot s holds column (c - b0) / 8: its place in the row is c moved from the
+  // vector buffer to the row; empty slots go to the spare cell.  (The zero
+  // cell's address is opaque per system: the slots' masks would otherwise be
+  // formed once per kernel and spill.)
+  unsigned zc = A.zc;
+  __asm__ volatile("" : "+v"(zc));
 #pragma unroll
-  for (int k0 = 0; k0 < RW::NZ; k0 += 4) {
-    int col[4];
+  for (int s = 0; s < RW::NZ; ++s)
+    lds_store<double>(A.c[0][s] != zc ? A.c[0][s] - A.b0 + fi : spare, A.a[0][s]);
+  wave_lds_fence();
+  // Three sets of registers in turn: a record's load is issued two records
+  // ahead, once the LDS reads of that time have arrived (scalar loads share
+  // the LDS counter out of order, and a load in flight at the reads' wait has
+  // to arrive too: issued just ahead of the reads it set the pace).
+  typedef const __attribute__((address_space(4))) uint16v* Records;
+  Records rec = (Records)(uintptr_t)g.ilu64;
+  double l = 0.0;
+  auto work = [&](const uint16v& w, uint16v& fresh, int ahead) {
+    unsigned fk = F + w[15];  // row k
+    const unsigned k8 = w[14] & 0x7fffffffu;
+    const bool first = w[14] >> 31;  // first record of pivot k
+    double piv = 1.0, aik = 0.0, u[4], f[4];
+    wave_lds_fence();
+    if (first) {
+      piv = lds_load<double>(fk + k8);
+      aik = lds_load<double>(fi + k8);
+    }
+    __asm__ volatile("" : "+v"(fk));  // one vector addition per column
 #pragma unroll
-    for (int k = k0; k < k0 + 4 && k < RW::NZ; ++k)
-      col[k - k0] = (int)lds_load<double>(A.c[0][k] + RW::kBuf);
+    for (int q = 0; q < 4; ++q) {
+      u[q] = lds_load<double>(fk + w[8 + q]);
+      f[q] = lds_load<double>(fi + w[8 + q]);
+    }
+    __asm__ volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(f[0]), "+v"(f[1]),
+                          "+v"(f[2]), "+v"(f[3]), "+v"(piv), "+v"(aik));
+    __builtin_amdgcn_sched_barrier(0);
+    fresh = rec[ahead];
+    if (first) {
+      l = aik / piv;
+      const uint64_t below = (uint64_t)w[13] << 32 | w[12];
+      lds_store<double>(__builtin_amdgcn_inverse_ballot_w64(below) ? fi + k8 : spare, l);
+    }
 #pragma unroll
-    for (int k = k0; k < k0 + 4 && k < RW::NZ; ++k)
-      if (ok && A.real(0, k)) {
-        F[i * st + col[k - k0]] = A.a[0][k];
-        mask |= 1ull << col[k - k0];
-      }
-    __asm__ volatile("" ::: "memory");
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t rows = (uint64_t)w[2 * q + 1] << 32 | w[2 * q];
+      lds_store<double>(__builtin_amdgcn_inverse_ballot_w64(rows) ? fi + w[8 + q] : spare,
+                        fma(-l, u[q], f[q]));
+    }
+  };
+  uint16v w0 = rec[0], w1 = rec[1], w2;
+  // a multiple of three records, and two empty ones that are read ahead
+  for (int r = g.ilu64_records; r > 0; r -= 3, rec += 3) {
+    work(w0, w2, 2);
+    work(w1, w0, 3);
+    work(w2, w1, 4);
   }
   wave_lds_fence();
-#pragma unroll 1
-  for (int k = 0; k + 1 < n; ++k) {
-    uint64_t cols = rdlane64(mask, k);
-    cols = k >= 63 ? 0 : cols & (~0ull << (k + 1));
-    const bool act = ok && i > k && ((mask >> k) & 1);
-    const double piv = F[k * st + k];
-    const double aik = F[i * st + k];
-    const double l = act ? aik / piv : 0.0;
-    if (act) F[i * st + k] = l;
-    while (cols) {  // wave-uniform
-      int j[kB];
-      bool has[kB];
-#pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        has[q] = cols != 0;
-        j[q] = has[q] ? __builtin_ctzll(cols) : k;
-        cols &= cols - 1;
-      }
-      double u[kB], f[kB];
-#pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        u[q] = F[k * st + j[q]];
-        f[q] = F[i * st + j[q]];
-      }
-      if (ok) {
-#pragma unroll
-        for (int q = 0; q < kB; ++q)
-          if (has[q]) F[i * st + j[q]] = ((mask >> j[q]) & 1) ? fma(-l, u[q], f[q]) : f[q];
-      }
-    }
-    wave_lds_fence();
-  }
   // a zero pivot or a non-finite entry: the identity for the whole system
-  bool bad = false;
-  if (ok) {
-    bad = F[i * st + i] == 0.0;
-    for (int j0 = 0; j0 < n; j0 += 8) {
-      double f[8];
+  // (0 * entry, summed over the row, is not a number then)
+  const double pivot = ok ? lds_load<double>(fi + i * 8) : 1.0;
+  double sum[2] = {0.0, 0.0};
+  for (int j = 0; j < st - 1; j += 8) {
+    double f[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) f[q] = F[i * st + j0 + q];
+    for (int q = 0; q < 8; ++q) f[q] = lds_load<double>(fi + (j + q) * 8);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) bad = bad || !__builtin_isfinite(f[q]);
-    }
+    for (int q = 0; q < 8; ++q) sum[q & 1] = fma(f[q], 0.0, sum[q & 1]);
   }
+  const bool bad = pivot == 0.0 || !__builtin_isfinite(sum[0] + sum[1]);
   if (wave_any(bad)) {
     wave_lds_fence();
-    for (int e = lane; e < n * st; e += kWave) F[e] = 0.0;
+    clear();
     d[0] = 1.0;
   } else {
-    d[0] = ok ? F[i * st + i] : 1.0;
+    d[0] = pivot;
   }
   wave_lds_fence();
 }
 
+// Eight consecutive doubles of a lane's row.
+struct Eight {
+  double v[8];
+};
+__device__ __forceinline__ Eight eight(unsigned at) {
+  Eight e;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) e.v[q] = lds_load<double>(at + q * 8);
+  return e;
+}
+
+// A column sweep over columns 0..n8-1 (n8 a multiple of 8, at most 64) of a
+// lane's row at fi, in increasing (UP) or decreasing order: step(k, entry).
+// Unrolled over all 64 columns, so that lanes and masks are constants (a lane
+// number from a scalar register costs a step 16 more cycles) and the reads of
+// the next eight entries issue in the gaps of a group's chain; groups past n8
+// are skipped.  A group reads ahead up to eight doubles past the row.
+template <bool UP, class STEP>
+__device__ __forceinline__ void sweep_columns(unsigned fi, int n8, STEP step) {
+  Eight t = eight(fi + (UP ? 0 : n8 - 8) * 8);
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {
+    const int k0 = UP ? 8 * h : 56 - 8 * h;
+    if (k0 < n8) {
+      // this group's entries first (read a group ago): issued behind the next
+      // group's reads, their wait would cover those too
+#pragma unroll
+      for (int q = 0; q < 8; ++q) __asm__ volatile("" : "+v"(t.v[q]));
+      Eight next = t;
+      if (h < 7) next = eight(fi + (UP ? k0 + 8 : k0 - 8) * 8);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) step(k0 + (UP ? q : 7 - q), t.v[UP ? q : 7 - q]);
+      t = next;
+    }
+  }
+}
+
+// a / d from 1 / d in two words, r + e: the error of the sum that is rounded is
+// under 2^-104 of the quotient, so the result is the correctly rounded one
+// unless the quotient lies that near to the middle of two doubles; two
+// dependent operations where the division takes about a dozen.  Holds while no
+// intermediate leaves the normal range, which quotient_safe() makes sure of.
+__device__ __forceinline__ double quotient(double a, double r, double e) { return fma(a, r, a * e); }
+__device__ __forceinline__ bool quotient_safe(double a, double d) {
+  const double x = fabs(a), y = fabs(d);
+  return (x == 0.0 || (x > 0x1p-500 && x < 0x1p500)) && y > 0x1p-400 && y < 0x1p400;
+}
+
 // z = (L U)^{-1} v by two column sweeps: forward, y_k (final on lane k) is
 // read out and every row i > k subtracts l_ik y_k; backward, z_j = y_j / u_jj
-// (a division by the pivot d of lane j) and every row i < j subtracts u_ij z_j.
-// Entries off the pattern, and the padding columns (read out from idle lanes,
-// whose values are zero and whose d is 1), add nothing.  The sums run in
+// (the quotient by the pivot d of lane j) and every row i < j subtracts u_ij
+// z_j.  The lanes that subtract are a mask formed in scalar registers.  Entries
+// off the pattern and the padding columns add nothing.  The sums run in
 // increasing k (forward) and decreasing j (backward).  With M the identity F
 // is zero and d = 1, so z = v.
+//
+// The sweeps are chains of n dependent steps and bound by a step's latency
+// (30 cycles forward, most of them the read-out of a lane and its first use):
+// 100 us per BiCGSTAB iteration of 16384 systems of 54 rows, where the rolled
+// form with divisions took 150.
+// A lane's value no longer changes once its step has passed, so one test
+// behind the backward sweep covers every quotient taken; out of range, the
+// sweep is repeated with divisions.
 template <class T, class TM, class RW>
 __device__ __forceinline__ void ilu_apply(TM& tm, const RW& A, const KArgs& g,
                                           const T (&d)[RW::R], const T (&v)[RW::R],
                                           T (&z)[RW::R]) {
   const int n = g.n, st = ilu_stride(n), n8 = st - 1;
-  const double* F = tm.bj_region(g);
   const bool ok = A.ok[0];
-  const int i = ok ? A.row[0] : 0;
-  const int ilo = ok ? i : kWave, ihi = ok ? i : -1;  // idle lanes take no term
-  const double dv = (double)d[0];
+  const unsigned fi = lds_addr(tm.bj_region(g)) + (unsigned)((ok ? A.row[0] : 0) * st) * 8;
+  const uint64_t rows = ~0ull >> (kWave - n);  // idle lanes take no term
+  const double dv = (double)d[0], r = 1.0 / dv, e = fma(-dv, r, 1.0) * r;
   double acc = ok ? (double)v[0] : 0.0;
-  for (int k0 = 0; k0 < n8; k0 += 8) {
-    double lk[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) lk[q] = F[i * st + k0 + q];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      acc = fma(ilo > k0 + q && ilo < kWave ? -lk[q] : 0.0, rdlane(acc, k0 + q), acc);
-  }
-  for (int j0 = n8 - 8; j0 >= 0; j0 -= 8) {
-    double uj[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) uj[q] = F[i * st + j0 + 7 - q];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const double zj = rdlane(acc / dv, j0 + 7 - q);
-      acc = fma(ihi < j0 + 7 - q && ihi >= 0 ? -uj[q] : 0.0, zj, acc);
+  sweep_columns<true>(fi, n8, [&](int k, double f) {
+    const double y = rdlane(acc, k);
+    if (__builtin_amdgcn_inverse_ballot_w64(lanes_past(k) & rows)) acc = fma(-f, y, acc);
+  });
+  const double y0 = acc;
+  sweep_columns<false>(fi, n8, [&](int j, double f) {
+    const double zj = rdlane(quotient(acc, r, e), j);
+    if (__builtin_amdgcn_inverse_ballot_w64(~(~0ull << j) & rows)) acc = fma(-f, zj, acc);
+  });
+  double zz = quotient(acc, r, e);
+  if (wave_any(!quotient_safe(acc, dv))) {
+    acc = y0;
+    for (int j = n - 1; j > 0; --j) {
+      const double zj = rdlane(acc / dv, j);
+      if (__builtin_amdgcn_inverse_ballot_w64(~(~0ull << j)))
+        acc = fma(-lds_load<double>(fi + j * 8), zj, acc);
     }
+    zz = acc / dv;
   }
-  z[0] = ok ? (T)(acc / dv) : (T)0;
+  z[0] = ok ? (T)zz : (T)0;
 }
 
 // ------------------------------------------------ ILU(0), multi-wave teams
@@ -966,40 +1044,45 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
 // BatchTrsv (Tab. 2): T x = b for T the lower (upper) triangle of A, diagonal
 // included, one-wave teams (row i on lane i, n <= 64).  The row's register
 // values outside the triangle are zeroed, so the shared epilogue's true
-// residual is that of T; the triangle goes to the LDS region as for ILU(0)
-// and one column sweep solves it: x_k = acc_k / t_kk (final on lane k when
-// column k is reached) is read out, and every later row subtracts t_ik x_k.
-// A zero diagonal entry is a breakdown (x = 0); iterations: 0.
+// residual is that of T; the triangle goes to the LDS region, packed by rows
+// (entry (i,j) of the lower one at i(i+1)/2 + j, of the upper one at i n -
+// i(i-1)/2 + j - i: half the square's LDS, twice the resident waves, and the
+// rows of a wave still start in distinct banks), and one column sweep solves
+// it: x_k = acc_k / t_kk (final on lane k when column k is reached) is read
+// out, and every later row subtracts t_ik x_k.  A sweep reads a lane's row at
+// every column; what lies there outside the triangle belongs to other rows,
+// and the lanes that would meet it take no term.  A zero diagonal entry is a
+// breakdown (x = 0); iterations: 0.
 template <bool LOWER, class TM, class RW>
 __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
   static_assert(RW::R == 1 && RW::TEAM == kWave, "one-wave BatchTrsv");
-  const int n = g.n, st = ilu_stride(n), n8 = st - 1;
-  double* F = tm.bj_region(g);
+  const int n = g.n, n8 = ilu_stride(n) - 1;
+  const unsigned F = lds_addr(tm.bj_region(g));
   const int lane = tm.lane;
   const bool ok = A.ok[0];
   const int i = ok ? A.row[0] : 0;
-  for (int e = lane; e < n * st; e += kWave) F[e] = 0.0;
-  if (ok) lds_store<double>(A.vrow[0] + RW::kBuf, (double)i);
-  tm.sync();
+  // byte address of column 0 of this lane's row
+  const unsigned fi = F + (unsigned)(LOWER ? i * (i + 1) / 2 : i * n - i * (i - 1) / 2 - i) * 8;
+  for (unsigned e = 16u * (unsigned)lane; e < (unsigned)trsv_bytes(n); e += 16u * kWave)
+    lds_store<uint4v>(F + e, uint4v{0, 0, 0, 0});
+  wave_lds_fence();
+  // slot s holds column (c - b0) / 8 (the zero cell, past all of them, when
+  // empty); entries outside the triangle go to the lane's own cell of buffer
+  // 0.  (vrow is opaque per system: the slots' masks would otherwise be formed
+  // once per kernel and spill.)
+  unsigned own = A.vrow[0];
+  __asm__ volatile("" : "+v"(own));
 #pragma unroll
-  for (int k0 = 0; k0 < RW::NZ; k0 += 4) {
-    int col[4];
-#pragma unroll
-    for (int k = k0; k < k0 + 4 && k < RW::NZ; ++k)
-      col[k - k0] = (int)lds_load<double>(A.c[0][k] + RW::kBuf);
-#pragma unroll
-    for (int k = k0; k < k0 + 4 && k < RW::NZ; ++k) {
-      const bool keep = ok && A.real(0, k) && (LOWER ? col[k - k0] <= i : col[k - k0] >= i);
-      if (keep) F[i * st + col[k - k0]] = A.a[0][k];
-      A.a[0][k] = keep ? A.a[0][k] : 0.0;
-    }
-    __asm__ volatile("" ::: "memory");
+  for (int s = 0; s < RW::NZ; ++s) {
+    const bool keep = LOWER ? A.c[0][s] <= own : A.c[0][s] - own < A.zc - own;
+    lds_store<double>(keep ? A.c[0][s] - A.b0 + fi : own, A.a[0][s]);
+    A.a[0][s] = keep ? A.a[0][s] : 0.0;
   }
   wave_lds_fence();
   double b[1] = {A.bval[0]}, x[1] = {A.xval[0]}, q[1] = {b[0] * b[0]};
   tm.sum(q);
   const double bn = sqrt(q[0]);
-  const double tii = ok ? F[i * st + i] : 1.0;
+  const double tii = ok ? lds_load<double>(fi + i * 8) : 1.0;
   int stt = tm.live ? ST_CONVERGED : ST_IDLE;
   if (tm.live && !finite(bn)) {
     stt = ST_NONFINITE;
@@ -1008,31 +1091,13 @@ __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
     x[0] = 0.0;
   } else {
     const double dv = ok ? 1.0 / tii : 0.0;
-    const int ilo = ok ? i : kWave, ihi = ok ? i : -1;  // idle lanes take no term
+    const uint64_t rows = ~0ull >> (kWave - n);  // idle lanes take no term
     double acc = ok ? b[0] : 0.0;
-    if constexpr (LOWER) {
-      for (int k0 = 0; k0 < n8; k0 += 8) {
-        double t[8];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) t[p] = F[i * st + k0 + p];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const double xk = rdlane(acc * dv, k0 + p);
-          acc = fma(ilo > k0 + p && ilo < kWave ? -t[p] : 0.0, xk, acc);
-        }
-      }
-    } else {
-      for (int j0 = n8 - 8; j0 >= 0; j0 -= 8) {
-        double t[8];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) t[p] = F[i * st + j0 + 7 - p];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const double xj = rdlane(acc * dv, j0 + 7 - p);
-          acc = fma(ihi < j0 + 7 - p && ihi >= 0 ? -t[p] : 0.0, xj, acc);
-        }
-      }
-    }
+    sweep_columns<LOWER>(fi, n8, [&](int k, double f) {
+      const double xk = rdlane(acc * dv, k);
+      if (__builtin_amdgcn_inverse_ballot_w64((LOWER ? lanes_past(k) : ~(~0ull << k)) & rows))
+        acc = fma(-f, xk, acc);
+    });
     x[0] = ok ? acc * dv : 0.0;
     if (tm.live && wave_any(ok && !finite(x[0]))) stt = ST_NONFINITE;
   }
@@ -1538,7 +1603,7 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned b, unsigned G) {
 // zero the compiler cannot see through: otherwise it hoists every argument
 // load out of the loop and keeps them all in scalar registers through the
 // solve, where they spill into vector-register lanes.
-#define BS_PERSISTENT_LOOP(MX, CALL)                                                \
+#define BS_PERSISTENT_LOOP(MX, PF, CALL)                                            \
   extern __shared__ __align__(16) char smem[];                                     \
   Team<S> tm(smem, g);                                                             \
   Rows<S, MX> A;                                                                   \
@@ -1546,8 +1611,11 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned b, unsigned G) {
   const int64_t stride = (int64_t)gridDim.x * S::TEAMS;                            \
   const int64_t slot0 = (int64_t)xcd_slot(blockIdx.x, gridDim.x) * S::TEAMS;      \
   bool staged = false;                                                             \
-  if constexpr (S::WAVES == 1) {                                                   \
-    staged = g.stage != 0;                                                         \
+  [[maybe_unused]] RegBlock<(PF)> pf;                                              \
+  if constexpr ((PF) > 0) {                                                        \
+    if (g.stage == 3 && slot0 < g.n_batch) A.prefetch_regs(tm, g, slot0, pf);      \
+  } else if constexpr (S::WAVES == 1) {                                            \
+    staged = g.stage == 1;                                                         \
     if (staged) A.prefetch(tm, g, slot0);                                          \
   } else if constexpr (S::NZ >= kStageMinSlots) {                                  \
     staged = g.stage == 2;                                                         \
@@ -1561,7 +1629,9 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned b, unsigned G) {
     tm.sys = base + tm.tix;                                                        \
     tm.live = tm.sys < ga.n_batch;                                                 \
     tm.row0 = tm.live ? tm.sys * ga.n : 0;                                         \
-    if constexpr (S::WAVES == 1) {                                                 \
+    if constexpr ((PF) > 0) {                                                      \
+      if (ga.stage == 3) A.put_regs(tm, ga, pf);                                   \
+    } else if constexpr (S::WAVES == 1) {                                          \
       if (staged) { /* the prefetch of this round has landed */                    \
         if (first_round) __builtin_amdgcn_s_waitcnt(0);                            \
         else __builtin_amdgcn_s_waitcnt(kWaitPrefetch);                            \
@@ -1576,7 +1646,10 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned b, unsigned G) {
       }                                                                            \
     }                                                                              \
     A.load_values(tm, ga);                                                         \
-    if constexpr (S::WAVES == 1) {                                                 \
+    if constexpr ((PF) > 0) {                                                      \
+      if (ga.stage == 3 && base + stride < ga.n_batch)                             \
+        A.prefetch_regs(tm, ga, base + stride, pf);                                \
+    } else if constexpr (S::WAVES == 1) {                                          \
       if (staged && base + stride < ga.n_batch) {                                  \
         __builtin_amdgcn_s_waitcnt(0xC07F); /* staging reads done (lgkmcnt 0) */   \
         __asm__ volatile("" ::: "memory");                                         \
@@ -1599,22 +1672,32 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned b, unsigned G) {
 template <class S, bool MIXED>
 constexpr bool kLds32 = MIXED && (S::ROWS > kWave);
 
+// One-wave ILU(0) and BatchTrsv: KiB of the next system's values kept in
+// registers through a solve (65536 triangular solves of 54 rows: 0.41 ms with
+// every lane reading its row from memory and a square triangle in LDS, 0.21 ms
+// with this and the packed one).  Their LDS goes to more resident waves instead of
+// a staging area, and a lane that reads its own row from memory touches a
+// line of its own with every load.
+template <class S>
+constexpr int kRegBlock = S::TEAM == kWave && S::R == 1 ? pf_chunks(S::NZ) : 0;
+
 // ILU(0) on one-wave teams: the dense factors (about 25 KB of LDS per wave
 // for 54 rows) leave room for fewer than two waves per SIMD, so the register
 // budget is that of two (no spills) rather than three.
 template <class S, bool MIXED, int PK = kPkScalar>
 __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu((MIXED || PK == kPkIlu) ? S::OCC_MIXED : S::OCC))) void k_bicgstab(const KArgs g) {
-  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (bicgstab_system<MIXED, PK>(tm, A, ga)))
+  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (PK == kPkIlu ? kRegBlock<S> : 0),
+                     (bicgstab_system<MIXED, PK>(tm, A, ga)))
 }
 
 template <class S, bool LOWER>
-__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC))) void k_trsv(const KArgs g) {
-  BS_PERSISTENT_LOOP(false, (trsv_system<LOWER>(tm, A, ga)))
+__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC_MIXED))) void k_trsv(const KArgs g) {
+  BS_PERSISTENT_LOOP(false, kRegBlock<S>, (trsv_system<LOWER>(tm, A, ga)))
 }
 
 template <class S, int PK = kPkScalar>
 __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC))) void k_cg(const KArgs g) {
-  BS_PERSISTENT_LOOP(false, (cg_system<PK>(tm, A, ga)))
+  BS_PERSISTENT_LOOP(false, 0, (cg_system<PK>(tm, A, ga)))
 }
 
 // GMRES keeps its basis in registers beside the row: held to three waves per
@@ -1623,7 +1706,7 @@ __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC)))
 // leaves room for only 2.5 anyway, so they are held to two, as the mixed ones.
 template <class S, bool MIXED, int PK = kPkScalar>
 __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC_MIXED))) void k_gmres(const KArgs g) {
-  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (gmres_system<MIXED, PK>(tm, A, ga)))
+  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), 0, (gmres_system<MIXED, PK>(tm, A, ga)))
 }
 
 #undef BS_PERSISTENT_LOOP
