@@ -24,8 +24,8 @@ namespace bs {
 namespace mlp {
 
 constexpr int kH = 256;     // hidden width
-constexpr int kTile = 64;   // samples per workgroup tile
-constexpr int kWG = 256;    // four waves
+constexpr int kTile = 64;   // samples of the largest workgroup tile
+constexpr int kWG = 256;    // lanes of the element-wise and weight-gradient kernels
 constexpr int kPad = 8;     // LDS row padding, elements
 constexpr int kMaxN = 64;   // largest system size (3n <= 192 features)
 
@@ -44,39 +44,6 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 
 __device__ __forceinline__ bf16x8 frag(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
-}
-
-// acc[rb][cb] += A[rb*16 .. +16][0..K) * B[0..K)[c0 + cb*16 .. +16]
-// A: LDS row-major, stride lda; Bt: global row-major [column][ldb].  The B
-// fragments of step k0 + 32 are loaded while the products of step k0 run (the
-// weights come from L2; waiting for them at every step left the matrix cores
-// idle); the products themselves run in the same order as without it.
-template <int RB, int CB>
-__device__ __forceinline__ void gemm_tile(floatx4 (&acc)[RB][CB], const uint16_t* A, int lda,
-                                          const uint16_t* __restrict__ Bt, int ldb, int c0, int K) {
-  const int l = threadIdx.x & 63, r16 = l & 15, q = l >> 4;
-  bf16x8 b[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) b[cb] = frag(Bt + (size_t)(c0 + cb * 16 + r16) * ldb + 8 * q);
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    bf16x8 a[RB], bn[CB];
-    if (k0 + 32 < K) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        bn[cb] = frag(Bt + (size_t)(c0 + cb * 16 + r16) * ldb + k0 + 32 + 8 * q);
-    }
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) a[rb] = frag(A + (rb * 16 + r16) * lda + k0 + 8 * q);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], b[cb], acc[rb][cb], 0, 0, 0);
-    if (k0 + 32 < K) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) b[cb] = bn[cb];
-    }
-  }
 }
 
 template <int RB, int CB>
@@ -122,8 +89,7 @@ struct Src {
 
 // Training outputs of the fused forward/backward kernel.
 struct Train {
-  int64_t M;                    // samples in the batch
-  int64_t Mp;                   // padded to the tile (leading dimension of the stores)
+  int64_t Mp;                   // samples padded to kTile (leading dimension of the stores)
   uint16_t* zT;                 // [Fp][Mp]
   uint16_t* h1T;                // [kH][Mp]
   uint16_t* h2T;                // [kH][Mp]
@@ -131,7 +97,6 @@ struct Train {
   uint16_t* dz2T;               // [kH][Mp]
   uint16_t* dyT;                // [Op][Mp]
   float* loss_part;             // [tiles] sum of squared errors of each tile
-  float* y_out;                 // optional [M][O] network outputs (tests)
 };
 
 }  // namespace mlp

@@ -99,7 +99,7 @@ constexpr WorkLayout work_layout(int Fp, int Op, int64_t Mp) {
   w.dy = off; off = align256(off + (size_t)Op * Mp * 2);
   w.part = off; off = align256(off + (size_t)chunks * w.part_ld * 4);
   w.bg = off; off = align256(off + (size_t)(2 * kH + Op) * 4);
-  w.lp = off; off = align256(off + (size_t)(Mp / kTile) * 4);
+  w.lp = off; off = align256(off + (size_t)(Mp / 16) * 4);
   w.total = off;
   return w;
 }
@@ -170,20 +170,72 @@ hipError_t launch_apply(const Apply& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Compute units of the current device (cached per device); -1 on an error.
+int compute_units() {
+  static int cache[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
+  if (cache[dev] == 0) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -1;
+    cache[dev] = v;
+  }
+  return cache[dev];
+}
+
+// Row blocks of 16 samples per tile (4, 2 or 1) of a training step over M
+// samples: the fewest rounds over the compute units, a round of RB row blocks
+// costing RB + 1 (a tile's fixed part, its weights and barriers, is worth about
+// one).  Whole steps of 54 unknowns on 256 units, tiles of 64 / 32 / 16
+// samples: 56 / 45 / 40 us for 4096 samples, 61 / 51 / 65 for 8192, 72 / 83 /
+// 95 for 12000, 315 / 372 / 537 for 65536.
+int train_row_blocks(int64_t M, int cus) {
+  int64_t best = INT64_MAX;
+  int rb = 4;
+  for (int r = 4; r >= 1; r /= 2) {
+    const int64_t tiles = (M + 16 * r - 1) / (16 * r), cost = (tiles + cus - 1) / cus * (r + 1);
+    if (cost < best) {
+      best = cost;
+      rb = r;
+    }
+  }
+  return rb;
+}
+
+// One forward pass over M systems or samples: a workgroup per compute unit
+// walks over the tiles with the weights held on chip.  Tiles of 16 while they
+// fit the units in one round, else of 32 (2^16 systems of 54 rows: 48 us, 52
+// in tiles of 16, and 61 in tiles of 64, whose inputs no longer fit the
+// registers beside the weights).
+template <int MODE>
+int launch_forward(const Net& net, const Src& src, float* y, int64_t M, hipStream_t st) {
+  const int cus = compute_units();
+  if (cus < 1) return BS_ERR_HIP;
+  const int rb = M <= (int64_t)16 * cus ? 1 : 2;
+  const int64_t tiles = (M + 16 * rb - 1) / (16 * rb);
+  const auto k = rb == 2 ? k_mlp_forward<MODE, 2> : k_mlp_forward<MODE, 1>;
+  hipLaunchKernelGGL(k, dim3((unsigned)std::min<int64_t>(tiles, cus)), dim3(kNetWG), 0, st, net, src, y,
+                     M, tiles);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? BS_OK : hip_err(e, "learned-start forward");
+}
+
 // Forward + backward over M samples and the gradient gather (and an Adam step
 // if update): the shared body of bs_ws_grad and bs_ws_train_step.
 int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, const float* delta,
              const int* rows, float* grad_out, float* loss_out, int update, float lr,
              hipStream_t st) {
   const int64_t Mp = (M + kTile - 1) / kTile * kTile;
-  const int tiles = (int)(Mp / kTile);
+  const int cus = compute_units();
+  if (cus < 1) return BS_ERR_HIP;
+  const int rb = train_row_blocks(Mp, cus);
+  const int tiles = (int)(Mp / (16 * rb));
   Src src;
   std::memset(&src, 0, sizeof src);
   src.feat = feat;
   src.delta = delta;
   src.rows = rows;
   Train tr;
-  tr.M = M;
   tr.Mp = Mp;
   tr.zT = w.zT;
   tr.h1T = w.h1T;
@@ -192,8 +244,8 @@ int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, cons
   tr.dz2T = w.dz2T;
   tr.dyT = w.dyT;
   tr.loss_part = w.loss_part;
-  tr.y_out = nullptr;
-  hipLaunchKernelGGL(k_mlp<kTrain>, dim3(tiles), dim3(kWG), 0, st, net_of(m), src, tr, M);
+  const auto train = rb == 4 ? k_mlp_train<4> : rb == 2 ? k_mlp_train<2> : k_mlp_train<1>;
+  hipLaunchKernelGGL(train, dim3(tiles), dim3(kNetWG), 0, st, net_of(m), src, tr, M);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_err(e, "learned-start forward/backward");
   WGrad g;
@@ -211,7 +263,7 @@ int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, cons
   g.nout[2] = m.Op;
   int start = 0;
   for (int L = 0; L < 3; ++L) {
-    g.tiles_c[L] = g.nout[L] / 32;
+    g.tiles_c[L] = (g.nout[L] + 63) / 64;
     g.tile_start[L] = start;
     start += (g.kin[L] / 64) * g.tiles_c[L];
   }
@@ -222,9 +274,6 @@ int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, cons
   g.chunk = kChunk;
   g.part = w.part;
   const int chunks = (int)((Mp + kChunk - 1) / kChunk);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3(start, chunks), dim3(kWG), 0, st, g);
-  e = hipGetLastError();
-  if (e != hipSuccess) return hip_err(e, "learned-start weight gradients");
   BGrad bg;
   bg.dT[0] = w.dz1T;
   bg.dT[1] = w.dz2T;
@@ -234,15 +283,14 @@ int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, cons
   bg.rows[2] = m.Op;
   bg.Mp = Mp;
   bg.out = w.bgrad;
-  hipLaunchKernelGGL(k_mlp_bgrad, dim3(2 * kH + m.Op), dim3(kWG), 0, st, bg);
+  bg.loss_part = w.loss_part;
+  bg.tiles = tiles;
+  bg.scale = 1.0 / ((double)M * m.O);
+  bg.loss = loss_out;
+  const int64_t blocks = (int64_t)start * chunks + 2 * kH + m.Op + (loss_out ? 1 : 0);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)blocks), dim3(kWG), 0, st, g, bg, chunks);
   e = hipGetLastError();
-  if (e != hipSuccess) return hip_err(e, "learned-start bias gradients");
-  if (loss_out) {
-    hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(64), 0, st, w.loss_part, tiles,
-                       1.0 / ((double)M * m.O), loss_out);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_err(e, "learned-start loss");
-  }
+  if (e != hipSuccess) return hip_err(e, "learned-start weight and bias gradients");
   Apply a = apply_of(m);
   a.part = w.part;
   a.part_ld = w.part_ld;
@@ -518,15 +566,7 @@ int bs_ws_forward(bs_ws_model m, int64_t n_samples, const float* feat, const int
   std::memset(&src, 0, sizeof src);
   src.feat = feat;
   src.rows = rows;
-  Train tr;
-  std::memset(&tr, 0, sizeof tr);
-  tr.M = n_samples;
-  tr.y_out = y;
-  const unsigned tiles = (unsigned)((n_samples + kTile - 1) / kTile);
-  hipLaunchKernelGGL(k_mlp<kForward>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, net_of(*m),
-                     src, tr, n_samples);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? BS_OK : hip_err(e, "learned-start forward");
+  return launch_forward<kForward>(net_of(*m), src, y, n_samples, (hipStream_t)stream);
 }
 
 int bs_ws_grad(bs_ws_model m, int64_t n_samples, const float* feat, const float* delta,
@@ -581,14 +621,7 @@ int bs_ws_infer(bs_ws_model m, int64_t n_batch, const double* values, const doub
   src.b = b;
   src.x_prev = x_prev;
   src.x0 = x0;
-  Train tr;
-  std::memset(&tr, 0, sizeof tr);
-  tr.M = n_batch;
-  const unsigned tiles = (unsigned)((n_batch + kTile - 1) / kTile);
-  hipLaunchKernelGGL(k_mlp<kInfer>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, net_of(*m), src,
-                     tr, n_batch);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? BS_OK : hip_err(e, "learned-start inference");
+  return launch_forward<kInfer>(net_of(*m), src, nullptr, n_batch, (hipStream_t)stream);
 }
 
 size_t bs_ws_packed_bytes(int32_t n) {
@@ -648,14 +681,7 @@ int bs_ws_infer_packed(int64_t n_batch, int32_t n, const void* weights, const do
   src.b = b;
   src.x_prev = x_prev;
   src.x0 = x0;
-  Train tr;
-  std::memset(&tr, 0, sizeof tr);
-  tr.M = n_batch;
-  const unsigned tiles = (unsigned)((n_batch + kTile - 1) / kTile);
-  hipLaunchKernelGGL(k_mlp<kInfer>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, t, src, tr,
-                     n_batch);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? BS_OK : hip_err(e, "learned-start inference (packed weights)");
+  return launch_forward<kInfer>(t, src, nullptr, n_batch, (hipStream_t)stream);
 }
 
 }  // extern "C"
