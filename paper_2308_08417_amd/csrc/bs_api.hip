@@ -21,16 +21,37 @@
 struct bs_pattern_s {
   int n = 0, nnz = 0, width = 0, max_row = 0, device = -1;
   std::vector<int> row_ptr, col, slot_col, row_len, diag_slot;
-  // level of each row in the lower and upper triangles' dependency graphs,
-  // packed (lower | upper << 16), and the level counts
-  std::vector<int> lev;
-  int nlev_l = 0, nlev_u = 0;
-  // ILU(0) schedule of the multi-wave factorization: per row (ilu_ptr), its
-  // steps in increasing pivot column k, a header word
-  // 1 << 31 | pos(k,k) << 15 | pos(i,k) followed by one word
-  // pos(k,j) << 16 | pos(i,j) per entry (i,j), j > k, that row k holds
-  // (positions in the pattern's CSR order)
+  // Multi-wave ILU(0) and BatchTrsv (patterns of up to 1024 rows).  The rows
+  // are taken by level in the lower (upper) triangle's dependency graph, the
+  // lower (upper) order; levels of the rows in lower order, their number, and
+  // the same rows' places in the upper order.
+  std::vector<int> lev, up;
+  int nlev = 0;
+  // Places of a row in the two orders (lower | upper << 16), and of each entry (CSR order) in the factor array
+  // (bs::IluMw); noff: entries off the diagonal.
+  std::vector<int> place;
+  std::vector<unsigned short> pos;
+  int noff = 0;
+  // ILU(0) schedule: the groups of row i, the q-th in lower order (from word
+  // ilu_ptr[q]), in increasing pivot column k, five words each: 1 << 31 | place of (k,k) << 15 | place of (i,k),
+  // or 0 when the group goes on with the last pivot; then four updates, place
+  // of (k,j) << 16 | place of (i,j), one per entry (i,j), j > k, that row k
+  // holds (filled up with the zero and the discard cell).
   std::vector<int> ilu_ptr, ilu_ops;
+  // Sweep segments: the rows of a level (at most 64 per step) with four of their
+  // strictly lower (upper) terms in increasing column, 2^w records of four
+  // words per segment, one per lane:
+  //   0, 1  byte offsets of the terms' columns in the sweep vector, 16 bits each
+  //         (the zero cell past the row's last term)
+  //   2     byte offsets of the row in the sweep's order and in the upper order
+  //         (the cell behind the zero cell on lanes without a row)
+  //   3     place of the first term in the factor array, terms << 16, 1 << 30 on
+  //         a row's first segment, 1 << 31 on its last
+  // Segments without rows make their number a multiple of four and are read
+  // four ahead.
+  std::vector<int> seg[2];
+  int nseg[2] = {0, 0}, wseg[2] = {0, 0};
+  bool one_seg[2] = {true, true};  // no row takes more than one segment
   // ILU(0) schedule of the one-wave factorization (patterns of up to 64 rows;
   // F is the factor array, row-major with stride ilu_stride(n)): for each pivot
   // k that a later row holds, in increasing order, its columns j > k that such
@@ -45,21 +66,15 @@ struct bs_pattern_s {
   // ahead.
   std::vector<int> ilu64;
   int ilu64_records = 0;
-  // Sweep lists of the multi-wave teams (ILU(0) substitutions, BatchTrsv):
-  // rows by lower level | rows by upper level | lower level starts (nlev_l+1)
-  // | upper level starts (nlev_u+1) | per row its list start (16 bits),
-  // lower and upper counts (8 bits each) | per row its strictly lower then
-  // strictly upper entries in increasing column, CSR position | column << 16.
-  std::vector<int> sweep;
-  int sweep_ents = 0;
   // bank-aware layout for one-wave teams of layout_nz register slots (0: none)
   std::vector<int> layout;
   int layout_nz = 0;
-  // one allocation: ilu64 | row_ptr | slot_col | row_len | diag_slot | lev |
-  // ilu_ptr | ilu_ops | sweep | layout
+  // one allocation: ilu64 | seg[0] | seg[1] | row_ptr | slot_col | row_len |
+  // diag_slot | lev | up | place | ilu_ptr | ilu_ops | pos | layout
   int* d_base = nullptr;
+  int *d_seg[2] = {nullptr, nullptr};
   int *d_row_ptr = nullptr, *d_slot_col = nullptr, *d_row_len = nullptr, *d_diag = nullptr;
-  int *d_lev = nullptr, *d_ilu_ptr = nullptr, *d_ilu_ops = nullptr, *d_sweep = nullptr;
+  int *d_lev = nullptr, *d_up = nullptr, *d_place = nullptr, *d_ilu_ptr = nullptr, *d_ilu_ops = nullptr, *d_pos = nullptr;
   int* d_layout = nullptr;
 };
 
@@ -105,6 +120,141 @@ int hip_fail(hipError_t e, const char* what) {
   return BS_ERR_HIP;
 }
 
+// The multi-wave triangular schedules hold rows and entries in 16-bit words.
+constexpr int kTriRows = 1024;
+
+// Level scheduling of a pattern's triangles (see bs_pattern_s): a row's lower
+// level is one more than the largest lower level among the columns j < i it
+// holds (0 if none), its upper level likewise over the columns j > i, taken
+// from the last row up.
+void tri_schedule(bs_pattern_s& p) {
+  const int n = p.n;
+  std::vector<int> level[2] = {std::vector<int>(n, 0), std::vector<int>(n, 0)};
+  for (int i = 0; i < n; ++i)
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
+      if (p.col[e] < i) level[0][i] = std::max(level[0][i], level[0][p.col[e]] + 1);
+  for (int i = n - 1; i >= 0; --i)
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
+      if (p.col[e] > i) level[1][i] = std::max(level[1][i], level[1][p.col[e]] + 1);
+  // rows by level, and each row's place among them
+  std::vector<int> order[2], at[2];
+  for (int t = 0; t < 2; ++t) {
+    order[t].resize(n);
+    at[t].resize(n);
+    for (int i = 0; i < n; ++i) order[t][i] = i;
+    std::stable_sort(order[t].begin(), order[t].end(),
+                     [&](int x, int y) { return level[t][x] < level[t][y]; });
+    for (int q = 0; q < n; ++q) at[t][order[t][q]] = q;
+  }
+  p.place.resize(n);
+  p.lev.resize(n);
+  p.up.resize(n);
+  for (int i = 0; i < n; ++i) p.place[i] = at[0][i] | (at[1][i] << 16);
+  for (int q = 0; q < n; ++q) {
+    p.lev[q] = level[0][order[0][q]];
+    p.up[q] = at[1][order[0][q]];
+  }
+  p.nlev = p.lev.back() + 1;
+  // each row's terms by increasing column, and their places
+  std::vector<std::vector<int>> terms[2];  // columns
+  std::vector<int> base[2];
+  p.pos.assign(p.nnz, 0);
+  p.noff = 0;
+  for (int t = 0; t < 2; ++t) {
+    terms[t].resize(n);
+    base[t].resize(n);
+  }
+  std::vector<std::pair<int, int>> row;
+  for (int i = 0; i < n; ++i) {
+    row.clear();
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) row.push_back({p.col[e], e});
+    std::sort(row.begin(), row.end());
+    for (int t = 0; t < 2; ++t) {
+      base[t][i] = p.noff;
+      for (const auto& c : row)
+        if (t == 0 ? c.first < i : c.first > i) {
+          p.pos[c.second] = (unsigned short)p.noff++;
+          terms[t][i].push_back(c.first);
+        }
+    }
+  }
+  const int diag0 = p.noff;
+  for (int i = 0; i < n; ++i)
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
+      if (p.col[e] == i) p.pos[e] = (unsigned short)(diag0 + at[1][i]);
+  // sweep segments
+  for (int t = 0; t < 2; ++t) {
+    std::vector<std::pair<int, int>> steps;  // first place, rows
+    for (int q = 0; q < n;) {
+      int c = 1;
+      while (c < bs::kWave && q + c < n && level[t][order[t][q + c]] == level[t][order[t][q]]) ++c;
+      steps.push_back({q, c});
+      q += c;
+    }
+    int w = 0;
+    for (const auto& st : steps)
+      while ((1 << w) < st.second) ++w;
+    p.wseg[t] = w;
+    p.seg[t].clear();
+    p.nseg[t] = 0;
+    p.one_seg[t] = true;
+    for (const auto& st : steps) {
+      size_t most = 1;
+      for (int l = 0; l < st.second; ++l) most = std::max(most, terms[t][order[t][st.first + l]].size());
+      p.one_seg[t] = p.one_seg[t] && most <= 4;
+      for (size_t k0 = 0; k0 < most; k0 += 4) {
+        for (int l = 0; l < (1 << w); ++l) {
+          const int i = l < st.second ? order[t][st.first + l] : -1;
+          unsigned col[4], r[4] = {0, 0, (unsigned)(n + 1) * 8 * 0x10001u, 0};
+          for (unsigned& c : col) c = (unsigned)n * 8;
+          if (i >= 0) {
+            const std::vector<int>& tm = terms[t][i];
+            int c = 0;
+            for (; c < 4 && k0 + c < tm.size(); ++c) col[c] = (unsigned)at[t][tm[k0 + c]] * 8;
+            r[2] = (unsigned)at[t][i] * 8 | ((unsigned)at[1][i] * 8 << 16);
+            r[3] = (unsigned)(c ? base[t][i] + (int)k0 : 0) | ((unsigned)c << 16) |
+                   (k0 == 0 ? 1u << 30 : 0u) | (k0 + 4 >= most ? 1u << 31 : 0u);
+          }
+          r[0] = col[0] | (col[1] << 16);
+          r[1] = col[2] | (col[3] << 16);
+          for (unsigned v : r) p.seg[t].push_back((int)v);
+        }
+        ++p.nseg[t];
+      }
+    }
+    const int total = (p.nseg[t] + 3) / 4 * 4;
+    for (int k = p.nseg[t]; k < total + 4; ++k)
+      for (int l = 0; l < (1 << w); ++l)
+        for (unsigned v : {(unsigned)n * 8 * 0x10001u, (unsigned)n * 8 * 0x10001u,
+                           (unsigned)(n + 1) * 8 * 0x10001u, 0u})
+          p.seg[t].push_back((int)v);
+    p.nseg[t] = total;
+  }
+  // The ILU(0) schedule (symbolic factorization, the IKJ form).
+  const unsigned discard = (unsigned)(diag0 + n), zero = discard + 1;
+  p.ilu_ptr.assign(n + 1, 0);
+  p.ilu_ops.clear();
+  std::vector<int> where(n, -1);
+  for (int q0 = 0; q0 < n; ++q0) {
+    const int i = order[0][q0];
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = e;
+    for (int k : terms[0][i]) {
+      std::vector<unsigned> up;
+      for (int e = p.row_ptr[k]; e < p.row_ptr[k + 1]; ++e) {
+        const int j = p.col[e];
+        if (j > k && where[j] >= 0) up.push_back((unsigned)p.pos[e] << 16 | p.pos[where[j]]);
+      }
+      for (size_t at0 = 0; at0 == 0 || at0 < up.size(); at0 += 4) {
+        p.ilu_ops.push_back(at0 ? 0 : (int)(1u << 31 | (unsigned)(diag0 + at[1][k]) << 15 | p.pos[where[k]]));
+        for (size_t q = at0; q < at0 + 4; ++q)
+          p.ilu_ops.push_back((int)(q < up.size() ? up[q] : zero << 16 | discard));
+      }
+    }
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = -1;
+    p.ilu_ptr[q0 + 1] = (int)p.ilu_ops.size();
+  }
+}
+
 // Derived per-row data shared by the CSR and ELL forms.
 void derive(bs_pattern_s& p) {
   const int n = p.n;
@@ -123,55 +273,7 @@ void derive(bs_pattern_s& p) {
   for (int s = 0; s < p.width; ++s)
     for (int i = 0; i < n; ++i)
       if (s < p.row_len[i]) p.slot_col[(size_t)s * n + i] = p.col[p.row_ptr[i] + s];
-  // Levels for the level-scheduled sweeps (ILU(0), BatchTrsv): a row's lower
-  // level is one more than the largest lower level among the columns j < i it
-  // holds (0 if none), its upper level likewise over the columns j > i, taken
-  // from the last row up.
-  std::vector<int> lo(n, 0), up(n, 0);
-  for (int i = 0; i < n; ++i)
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-      if (p.col[e] < i) lo[i] = std::max(lo[i], lo[p.col[e]] + 1);
-  for (int i = n - 1; i >= 0; --i)
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-      if (p.col[e] > i) up[i] = std::max(up[i], up[p.col[e]] + 1);
-  p.lev.resize(n);
-  p.nlev_l = p.nlev_u = 0;
-  for (int i = 0; i < n; ++i) {
-    // 16 bits each: the multi-wave paths that read it take at most 1024 rows
-    p.lev[i] = (int)(((unsigned)lo[i] & 0xffffu) | ((unsigned)up[i] << 16));
-    p.nlev_l = std::max(p.nlev_l, lo[i] + 1);
-    p.nlev_u = std::max(p.nlev_u, up[i] + 1);
-  }
-  // The ILU(0) schedule (symbolic factorization, the IKJ form): for row i and
-  // each column k < i it holds, in increasing k, divide (i,k) by the pivot
-  // (k,k), then update each (i,j), j > k, for which row k holds (k,j).  A row
-  // without a stored diagonal divides by its own entry instead: the system
-  // then has a zero pivot and its preconditioner is the identity anyway.  Only
-  // patterns whose positions fit 15 bits get one (the multi-wave shapes hold
-  // at most 16384 entries).
-  p.ilu_ptr.assign(n + 1, 0);
-  p.ilu_ops.clear();
-  if (p.nnz < (1 << 15)) {
-    std::vector<int> where(n, -1), ks;
-    for (int i = 0; i < n; ++i) {
-      for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = e;
-      ks.clear();
-      for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-        if (p.col[e] < i) ks.push_back(p.col[e]);
-      std::sort(ks.begin(), ks.end());
-      for (int k : ks) {
-        const int pik = where[k];
-        const int pkk = p.diag_slot[k] >= 0 ? p.row_ptr[k] + p.diag_slot[k] : pik;
-        p.ilu_ops.push_back((int)(0x80000000u | ((unsigned)pkk << 15) | (unsigned)pik));
-        for (int e = p.row_ptr[k]; e < p.row_ptr[k + 1]; ++e) {
-          const int j = p.col[e];
-          if (j > k && where[j] >= 0) p.ilu_ops.push_back((e << 16) | where[j]);
-        }
-      }
-      for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = -1;
-      p.ilu_ptr[i + 1] = (int)p.ilu_ops.size();
-    }
-  }
+  if (n <= kTriRows && p.nnz < (1 << 15)) tri_schedule(p);
   // The one-wave schedule: rows and columns as 64-bit masks.
   p.ilu64.clear();
   if (n <= bs::kWave) {
@@ -207,51 +309,6 @@ void derive(bs_pattern_s& p) {
     p.ilu64_records = (int)(p.ilu64.size() / 16 + 2) / 3 * 3;
     p.ilu64.resize((size_t)(p.ilu64_records + 2) * 16, 0);
   }
-  // Sweep lists (same 15-bit positions; rows of up to 255 entries per triangle;
-  // columns below 2^15).
-  p.sweep.clear();
-  p.sweep_ents = 0;
-  if (p.nnz < (1 << 15) && n < (1 << 15)) {
-    std::vector<int> by_l(n), by_u(n), start_l(p.nlev_l + 1, 0), start_u(p.nlev_u + 1, 0);
-    for (int i = 0; i < n; ++i) {
-      ++start_l[lo[i] + 1];
-      ++start_u[up[i] + 1];
-    }
-    for (int l = 0; l < p.nlev_l; ++l) start_l[l + 1] += start_l[l];
-    for (int l = 0; l < p.nlev_u; ++l) start_u[l + 1] += start_u[l];
-    std::vector<int> fill_l(start_l.begin(), start_l.end() - 1), fill_u(start_u.begin(), start_u.end() - 1);
-    for (int i = 0; i < n; ++i) {
-      by_l[fill_l[lo[i]]++] = i;
-      by_u[fill_u[up[i]]++] = i;
-    }
-    std::vector<int> rng(n), ent;
-    std::vector<std::pair<int, int>> lw, uw;
-    bool fits = true;
-    for (int i = 0; i < n && fits; ++i) {
-      lw.clear();
-      uw.clear();
-      for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) {
-        if (p.col[e] < i) lw.push_back({p.col[e], e});
-        if (p.col[e] > i) uw.push_back({p.col[e], e});
-      }
-      std::sort(lw.begin(), lw.end());
-      std::sort(uw.begin(), uw.end());
-      fits = lw.size() < 256 && uw.size() < 256;
-      rng[i] = (int)((unsigned)ent.size() | ((unsigned)lw.size() << 16) | ((unsigned)uw.size() << 24));
-      for (const auto& q : lw) ent.push_back(q.second | (q.first << 16));
-      for (const auto& q : uw) ent.push_back(q.second | (q.first << 16));
-    }
-    if (fits) {
-      p.sweep_ents = (int)ent.size();
-      p.sweep.reserve(3 * n + p.nlev_l + p.nlev_u + 2 + ent.size());
-      p.sweep.insert(p.sweep.end(), by_l.begin(), by_l.end());
-      p.sweep.insert(p.sweep.end(), by_u.begin(), by_u.end());
-      p.sweep.insert(p.sweep.end(), start_l.begin(), start_l.end());
-      p.sweep.insert(p.sweep.end(), start_u.begin(), start_u.end());
-      p.sweep.insert(p.sweep.end(), rng.begin(), rng.end());
-      p.sweep.insert(p.sweep.end(), ent.begin(), ent.end());
-    }
-  }
 }
 
 int upload(bs_pattern_s& p) {
@@ -263,36 +320,37 @@ int upload(bs_pattern_s& p) {
   }
   hipError_t e = hipGetDevice(&p.device);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  const size_t n_rp = p.n + 1, n_sc = std::max<size_t>((size_t)p.width * p.n, 1), n_rl = p.n;
-  const size_t n_ops = std::max<size_t>(p.ilu_ops.size(), 1);
-  const size_t n_sw = std::max<size_t>(p.sweep.size(), 1);
-  // (ilu64 first: its 64-byte records are aligned to their size)
-  const size_t n_i64 = p.ilu64.size();
-  const size_t total = n_i64 + n_rp + n_sc + 3 * n_rl + n_rp + n_ops + n_sw + p.layout.size();
+  // the regions in order: the schedules read 16 or 64 bytes at a time first
+  std::vector<int> h;
+  auto put = [&](const auto& v, size_t least = 0) {
+    const size_t off = h.size();
+    h.insert(h.end(), v.begin(), v.end());
+    h.resize(std::max(h.size(), off + least), -1);
+    return off;
+  };
+  std::vector<int> pos((p.pos.size() + 1) / 2, 0);
+  if (!p.pos.empty()) std::memcpy(pos.data(), p.pos.data(), p.pos.size() * sizeof(unsigned short));
+  put(p.ilu64);
+  const size_t o_seg0 = put(p.seg[0]), o_seg1 = put(p.seg[1]);
+  const size_t o_rp = put(p.row_ptr), o_sc = put(p.slot_col, 1), o_rl = put(p.row_len),
+               o_ds = put(p.diag_slot), o_lev = put(p.lev), o_up = put(p.up), o_place = put(p.place),
+               o_ptr = put(p.ilu_ptr), o_ops = put(p.ilu_ops), o_pos = put(pos), o_lay = put(p.layout);
+  const size_t total = h.size();
   e = hipMalloc(&p.d_base, total * sizeof(int));
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(pattern)");
-  p.d_row_ptr = p.d_base + n_i64;
-  p.d_slot_col = p.d_row_ptr + n_rp;
-  p.d_row_len = p.d_slot_col + n_sc;
-  p.d_diag = p.d_row_len + n_rl;
-  p.d_lev = p.d_diag + n_rl;
-  p.d_ilu_ptr = p.d_lev + n_rl;
-  p.d_ilu_ops = p.d_ilu_ptr + n_rp;
-  p.d_sweep = p.d_ilu_ops + n_ops;
-  p.d_layout = p.layout.empty() ? nullptr : p.d_sweep + n_sw;
-  std::vector<int> h(total, -1);
-  const auto at = h.begin() + n_i64;
-  std::copy(p.ilu64.begin(), p.ilu64.end(), h.begin());
-  const size_t o_lev = n_rp + n_sc + 2 * n_rl, o_ptr = o_lev + n_rl, o_ops = o_ptr + n_rp;
-  std::copy(p.lev.begin(), p.lev.end(), at + o_lev);
-  std::copy(p.ilu_ptr.begin(), p.ilu_ptr.end(), at + o_ptr);
-  std::copy(p.ilu_ops.begin(), p.ilu_ops.end(), at + o_ops);
-  std::copy(p.sweep.begin(), p.sweep.end(), at + o_ops + n_ops);
-  std::copy(p.layout.begin(), p.layout.end(), at + o_ops + n_ops + n_sw);
-  std::copy(p.row_ptr.begin(), p.row_ptr.end(), at);
-  std::copy(p.slot_col.begin(), p.slot_col.end(), at + n_rp);
-  std::copy(p.row_len.begin(), p.row_len.end(), at + n_rp + n_sc);
-  std::copy(p.diag_slot.begin(), p.diag_slot.end(), at + n_rp + n_sc + n_rl);
+  p.d_seg[0] = p.d_base + o_seg0;
+  p.d_seg[1] = p.d_base + o_seg1;
+  p.d_row_ptr = p.d_base + o_rp;
+  p.d_slot_col = p.d_base + o_sc;
+  p.d_row_len = p.d_base + o_rl;
+  p.d_diag = p.d_base + o_ds;
+  p.d_lev = p.d_base + o_lev;
+  p.d_up = p.d_base + o_up;
+  p.d_place = p.d_base + o_place;
+  p.d_ilu_ptr = p.d_base + o_ptr;
+  p.d_ilu_ops = p.d_base + o_ops;
+  p.d_pos = p.d_base + o_pos;
+  p.d_layout = p.layout.empty() ? nullptr : p.d_base + o_lay;
   e = hipMemcpy(p.d_base, h.data(), total * sizeof(int), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(p.d_base);
@@ -500,6 +558,9 @@ int make_plan(bs_format fmt, int n, int nnz, int max_row, int width, bs_solver s
   out->info.stage_values = stage;
   // a workgroup's LDS is at most that of a compute unit
   if (out->info.lds_bytes > kLdsPerCu) return BS_ERR_UNSUPPORTED;
+  if (tri && team > bs::kWave &&
+      vec - bs::tri_region_bytes(team, n, nnz, trsv) + bs::tri_limit_bytes(n, nnz) > kLdsPerCu)
+    return BS_ERR_UNSUPPORTED;
   return BS_OK;
 }
 
@@ -817,8 +878,8 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
     streamed = rc == BS_OK;
   }
   if (rc != BS_OK) return rc;
-  // multi-wave ILU(0) and BatchTrsv need the pattern's sweep lists
-  if (!streamed && (ilu || trsv) && pl.info.team > bs::kWave && pattern->sweep.empty())
+  // multi-wave ILU(0) and BatchTrsv need the pattern's schedules
+  if (!streamed && (ilu || trsv) && pl.info.team > bs::kWave && pattern->lev.empty())
     return BS_ERR_UNSUPPORTED;
   bs::KArgs a{};
   a.n_batch = n_solves;
@@ -868,14 +929,23 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   a.row_len = pattern->d_row_len;
   a.diag_slot = pattern->d_diag;
   a.lev = pattern->d_lev;
-  a.nlev_l = pattern->nlev_l;
-  a.nlev_u = pattern->nlev_u;
+  a.nlev = pattern->nlev;
+  a.tri_up = pattern->d_up;
   a.ilu_ptr = pattern->d_ilu_ptr;
   a.ilu_ops = pattern->d_ilu_ops;
+  a.tri_place = pattern->d_place;
+  a.tri_pos = reinterpret_cast<const unsigned short*>(pattern->d_pos);
+  a.seg_l = reinterpret_cast<const int4*>(pattern->d_seg[0]);
+  a.seg_u = reinterpret_cast<const int4*>(pattern->d_seg[1]);
+  a.nseg_l = pattern->nseg[0];
+  a.nseg_u = pattern->nseg[1];
+  a.wseg_l = pattern->wseg[0];
+  a.wseg_u = pattern->wseg[1];
+  a.one_l = pattern->one_seg[0];
+  a.one_u = pattern->one_seg[1];
+  a.noff = pattern->noff;
   a.ilu64 = pattern->d_base;
   a.ilu64_records = pattern->ilu64_records;
-  a.sweep = pattern->d_sweep;
-  a.sweep_ents = pattern->sweep_ents;
   a.values = values;
   a.b = b;
   a.x = x;

@@ -220,8 +220,9 @@ struct Team {
   char* stage;      // this team's part of it: values, then b
   double* red;      // cross-wave reduction slots (multi-wave teams)
   int phase;        // which half of `red` the next reduction uses
-  bool lists;       // the pattern's sweep lists are in LDS (multi-wave ILU(0), BatchTrsv)
-
+  bool lists;       // the constant cells are set (multi-wave ILU(0), BatchTrsv)
+  bool divide;      // pivots outside the range of the reciprocal form (multi-wave ILU(0))
+  unsigned place;   // this lane's row in the sweeps' orders (multi-wave ILU(0))
 
   __device__ Team(char* smem, const KArgs& a) {
     const int t = threadIdx.x;
@@ -235,7 +236,8 @@ struct Team {
     stage = a.stage == 3 ? lds + a.bj_offset : stage_all + (size_t)tix * a.stage_team_bytes;
     red = reinterpret_cast<double*>(smem + (size_t)S::TEAMS * a.team_bytes);
     phase = 0;
-    lists = false;
+    lists = divide = false;
+    place = 0;
   }
 
   // Make this team's LDS writes visible to all of its lanes.  A single-wave

@@ -53,15 +53,20 @@ struct KArgs {
   int nrhs;                    // right-hand sides per matrix: solve s reads matrix s / nrhs
   int block;                   // block-Jacobi block size (2, 4 or 8), 0 for scalar Jacobi / none
   int bj_offset;               // byte offset of the block-Jacobi or ILU(0) region in a team's LDS
-  const int* lev;              // [n] row levels for the sweeps of multi-wave teams:
-                               // lower-triangle level | upper-triangle level << 16
-  int nlev_l, nlev_u;          // level counts of the lower and upper triangles
-  const int* ilu_ptr;          // [n+1] start of each row's ILU(0) steps in ilu_ops
-  const int* ilu_ops;          // ILU(0) schedule (header and update words, see the pattern)
+  const int* lev;              // [n] lower-triangle levels of the rows in lower order
+  int nlev;                    // their number (multi-wave ILU(0))
+  const int* tri_up;           // [n] places in the upper order of the rows in lower order
+  const int* ilu_ptr;          // [n+1] first word of each such row's ILU(0) groups in ilu_ops
+  const int* ilu_ops;          // ILU(0) schedule of multi-wave teams (see the pattern)
+  const int* tri_place;        // [n] places of a row in the lower and upper orders
+  const unsigned short* tri_pos;  // [nnz] place of each entry in the factor array
+  const int4 *seg_l, *seg_u;   // sweep segments of multi-wave teams, and their number and
+  int nseg_l, nseg_u;          // (log2) width
+  int wseg_l, wseg_u;
+  int one_l, one_u;            // every row fits one segment
+  int noff;                    // entries off the diagonal
   const int* ilu64;            // ILU(0) records of one-wave teams (see the pattern)
   int ilu64_records;
-  const int* sweep;            // sweep lists of multi-wave teams (see the pattern)
-  int sweep_ents;              // entries in those lists
 };
 
 // Matrix of solve s (several right-hand sides per matrix: solves s*k..s*k+k-1
@@ -192,25 +197,34 @@ inline int stage_total_bytes(int teams, int stored, int n, int nz) {
 
 // ILU(0) and BatchTrsv of a multi-wave team (row i on lane i, one row per
 // lane): byte offsets inside the team's region of the factor (or triangle)
-// values in the pattern's CSR order (f, nnz doubles), the sweep vector (y, n
-// doubles), the pivots or diagonal (d, n doubles), and the pattern's sweep
-// lists: per row its list start and counts (rng, n ints), the lists (ent, at
-// most nnz ints), the rows in level order (rows, 2n shorts) and the level
-// starts (lvl, at most 2n+2 shorts).
+// values (f: the entries off the diagonal, row by row, the strictly lower ones
+// in increasing column, then the strictly upper ones; the n diagonal entries, in
+// the order of the sweep that divides by them; a cell to discard into and a
+// zero), the diagonal's reciprocals in two words (re, pairs in the same order),
+// the sweep vector in the order of the sweep at hand (y), and the right-hand
+// side of the sweep that divides (v); y has a zero cell behind its n entries,
+// and all three a cell behind that for lanes without a row.
 struct IluMw {
-  int f, y, d, rng, ent, rows, lvl, bytes;
+  int f, re, y, v, bytes;
 };
 __host__ __device__ constexpr IluMw ilu_mw_layout(int n, int nnz) {
-  const int y = round16(nnz * 8), d = y + round16(n * 8), rng = d + round16(n * 8);
-  const int ent = rng + round16(n * 4), rows = ent + round16(nnz * 4);
-  const int lvl = rows + round16(n * 4);
-  return IluMw{0, y, d, rng, ent, rows, lvl, lvl + round16((2 * n + 2) * 2)};
+  const int re = round16((nnz + n + 2) * 8), y = re + (n + 2) * 16, v = y + round16((n + 2) * 8);
+  return IluMw{0, re, y, v, v + round16((n + 2) * 8)};
 }
 
 // LDS bytes of a team's ILU(0) or BatchTrsv region: the dense factors or the
 // packed triangle of a one-wave team, the sparse layout above for larger teams.
 __host__ __device__ constexpr int tri_region_bytes(int team, int n, int nnz, bool trsv) {
   return team > kWave ? ilu_mw_layout(n, nnz).bytes : trsv ? trsv_bytes(n) : ilu_bytes(n);
+}
+
+// Accepted sizes of a multi-wave ILU(0) or BatchTrsv: this many bytes, 12 per
+// entry and 28 per row, have to fit a compute unit's LDS beside the vectors.
+// The layout above takes no more from 3 entries per row on, and the limit
+// stays where callers know it.
+__host__ __device__ constexpr int tri_limit_bytes(int n, int nnz) {
+  return round16(nnz * 8) + 2 * round16(n * 8) + 2 * round16(n * 4) + round16(nnz * 4) +
+         round16((2 * n + 2) * 2);
 }
 
 }  // namespace bs

@@ -422,222 +422,252 @@ __device__ __forceinline__ void ilu_apply(TM& tm, const RW& A, const KArgs& g,
 
 // ------------------------------------------------ ILU(0), multi-wave teams
 // Teams of 2..16 waves (row i on lane i, one row per lane, up to 1024 rows)
-// keep the factors sparse, in the pattern's CSR order, and run the
-// factorization and both sweeps level by level (level scheduling; Saad 2003,
-// Ch. 11): a row's level in the lower triangle is one more than the largest
-// level among the rows its strictly lower entries name (0 if none), and its
-// level in the upper triangle is defined the same way from its strictly upper
-// entries.  Rows of one level depend only on earlier levels.  The
-// factorization takes one level per team barrier, each lane its own row; the
-// sweeps run on the team's first wave alone, whose LDS operations complete in
-// issue order, so that levels follow one another without a barrier.  The
-// levels, the factorization schedule and the sweep lists come with the
+// keep the factors sparse (bs::IluMw) and run the factorization and both sweeps
+// level by level (level scheduling; Saad 2003, Ch. 11): a row's level in the
+// lower triangle is one more than the largest level among the rows its strictly
+// lower entries name (0 if none), and its level in the upper triangle is
+// defined the same way from its strictly upper entries.  Rows of one level
+// depend only on earlier levels.  The factorization takes one level per team
+// barrier, each lane its own row; the sweeps run on the team's first wave
+// alone, whose LDS operations complete in issue order, so that levels follow
+// one another without a barrier.  The levels and schedules come with the
 // pattern.
 
-// The pattern's sweep lists into the team's region, once per kernel (they are
-// the same for every system): rows in lower then upper level order and the
-// level starts as 16-bit values, each row's list start and counts, the lists.
+// The region's constant cells, once per kernel: the zero of the factor array
+// and the one behind the sweep vector.  (The next barrier orders them.)
 template <class TM>
-__device__ __forceinline__ void sweep_lists_load(TM& tm, const KArgs& g, unsigned reg,
-                                                 const IluMw& L) {
+__device__ __forceinline__ void tri_cells(TM& tm, const KArgs& g, unsigned reg, const IluMw& L) {
   if (tm.lists) return;
-  const int n = g.n, nl = g.nlev_l + g.nlev_u + 2;
-  const int* sw = g.sweep;
-  for (int t = threadIdx.x; t < 2 * n; t += blockDim.x)
-    lds_store<short>(reg + L.rows + t * 2, (short)sw[t]);
-  for (int t = threadIdx.x; t < nl; t += blockDim.x)
-    lds_store<short>(reg + L.lvl + t * 2, (short)sw[2 * n + t]);
-  for (int t = threadIdx.x; t < n; t += blockDim.x)
-    lds_store<int>(reg + L.rng + t * 4, sw[2 * n + nl + t]);
-  for (int t = threadIdx.x; t < g.sweep_ents; t += blockDim.x)
-    lds_store<int>(reg + L.ent + t * 4, sw[3 * n + nl + t]);
+  if (threadIdx.x == 0) {
+    lds_store<double>(reg + L.f + (g.noff + g.n) * 8, 0.0);
+    lds_store<double>(reg + L.f + (g.noff + g.n + 1) * 8, 0.0);
+    lds_store<double>(reg + L.y + g.n * 8, 0.0);
+  }
   tm.lists = true;
 }
 
-// One triangular sweep over the team's sweep vector y, run by the team's first
-// wave: for the rows of each level in turn, lane t takes the level's t-th row r
-// (then the (t+64)-th, ...) and sets y_r <- (y_r - sum_c t_rc y_c) [/ d_r] over
-// the row's strictly lower (LOWER) or upper entries in increasing column, t_rc
-// from the values at their CSR positions; DIV divides by d_r.  Pipelined so
-// that only this level's gathers wait on the previous level: the level ends
-// are read two levels ahead, the next level's first row before this level's
-// list words, and that row's list range once this level's loads are out.
-template <bool LOWER, bool DIV>
-__device__ __forceinline__ void tri_sweep(const KArgs& g, unsigned reg, const IluMw& L) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const unsigned F = reg + L.f, Y = reg + L.y, D = reg + L.d, RNG = reg + L.rng, ENT = reg + L.ent;
-  const unsigned ROWS = reg + L.rows + (LOWER ? 0 : g.n * 2);
-  const unsigned LVL = reg + L.lvl + (LOWER ? 0 : (g.nlev_l + 1) * 2);
-  const int nlev = LOWER ? g.nlev_l : g.nlev_u;
-  // y_r update of one row from its list range gg (the list words, then the
-  // values and gathers, four terms at a time)
-  auto row = [&](int rr, unsigned gg) {
-    const int lc = (int)((gg >> 16) & 0xffu);
-    const int e0 = (int)(gg & 0xffffu) + (LOWER ? 0 : lc);
-    const int e1 = e0 + (LOWER ? lc : (int)(gg >> 24));
-    double acc = lds_load<double>(Y + rr * 8);
-    for (int e = e0; e < e1; e += 4) {
-      unsigned w[4];
-      double f[4], y[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = e + k < e1 ? lds_load<unsigned>(ENT + (e + k) * 4) : 0u;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        f[k] = e + k < e1 ? lds_load<double>(F + (w[k] & 0x7fffu) * 8) : 0.0;
-        y[k] = e + k < e1 ? lds_load<double>(Y + (w[k] >> 16) * 8) : 0.0;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (e + k < e1) acc = fma(-f[k], y[k], acc);
-    }
-    if (DIV) acc = acc / lds_load<double>(D + rr * 8);
-    lds_store<double>(Y + rr * 8, acc);
+// One triangular sweep by the team's first wave: for the rows of each level
+// in turn, out_r <- (in_r - sum_c t_rc out_c) [/ d_r] (DIV), the row's strictly
+// lower or upper terms in increasing column, rows at their places in the
+// sweep's order.  COPY also stores the result at the row's place in the upper
+// order.  SEL: the values may be other than finite, so the ones past a row's
+// last term are replaced by zero (otherwise they meet the zero cell).  ONE: no
+// row takes more than one segment; lanes without a row then store like the
+// others, to the cell kept for them.  `divide`: by division instead of the
+// reciprocal in two words.
+//
+// A segment (the four first terms of a level's rows, then the next four ..) is
+// one record per lane, read from memory four segments ahead; everything but the
+// gathers of the sweep vector is read from LDS one segment ahead, so a level
+// waits for its gathers, four multiplications, the quotient and the store.
+// Bound by the issue of one wave's instructions, about 40 per segment.
+// Finding a row, its list range, its list words and then its values and
+// gathers one after another in LDS took 700 cycles per level of the 992-row
+// stencil (up to 16 rows), now 200.
+template <bool DIV, bool SEL, bool COPY, bool ONE>
+__device__ __forceinline__ void tri_sweep(const int4* __restrict__ segs, int nseg, int w, unsigned F,
+                                          unsigned in, unsigned out, unsigned D, unsigned RE,
+                                          unsigned copy, bool divide) {
+  const int4* rec = segs + (threadIdx.x & ((1 << w) - 1));
+  struct Seg {
+    double f[4], a, r, e;
+    unsigned c0, c1, own, tag;
   };
-  int qa = lds_load<short>(LVL), qb = lds_load<short>(LVL + 2);
-  int qc = nlev > 1 ? lds_load<short>(LVL + 4) : qb;  // end of the next level
-  int r = qa + lane < qb ? lds_load<short>(ROWS + (qa + lane) * 2) : -1;
-  unsigned rg = r >= 0 ? lds_load<unsigned>(RNG + r * 4) : 0u;
-  for (int l = 0; l < nlev; ++l) {
-    const int qd = l + 2 < nlev ? lds_load<short>(LVL + (l + 3) * 2) : qc;
-    const int nr = qb + lane < qc ? lds_load<short>(ROWS + (qb + lane) * 2) : -1;
-    // This level's first row on each lane, rows of up to four terms without
-    // branches: list words at clamped indices, words past the row's count (and
-    // on lanes without a row) replaced by 0 (entry 0, column 0: valid
-    // addresses), their terms dropped by selection.  The next row's list range
-    // is read once this level's loads are out.
-    const int lc = (int)((rg >> 16) & 0xffu);
-    const int e0 = (int)(rg & 0xffffu) + (LOWER ? 0 : lc);
-    const int ne = r >= 0 ? (LOWER ? lc : (int)(rg >> 24)) : 0;
-    const int rs = r >= 0 ? r : 0;
-    const int last = g.sweep_ents > 0 ? g.sweep_ents - 1 : 0;
-    unsigned w[4];
-    double f[4], y[4];
+  auto fetch = [&](const int4& q) {
+    Seg s;
+    s.c0 = (unsigned)q.x;
+    s.c1 = (unsigned)q.y;
+    s.own = (unsigned)q.z;
+    s.tag = (unsigned)q.w;
+    const unsigned fa = F + (s.tag & 0x7fffu) * 8, o = s.own & 0xffffu;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const unsigned wk = lds_load<unsigned>(ENT + min(e0 + k, last) * 4);
-      w[k] = k < ne ? wk : 0u;
+    for (int k = 0; k < 4; ++k) s.f[k] = lds_load<double>(fa + k * 8);
+    s.a = lds_load<double>(in + o);
+    if constexpr (DIV) {
+      typedef double double2v __attribute__((ext_vector_type(2)));
+      const double2v re = lds_load<double2v>(RE + o * 2);
+      s.r = re.x;
+      s.e = re.y;
+    } else {
+      s.r = s.e = 0.0;
     }
-    const double y0 = lds_load<double>(Y + rs * 8);
+    return s;
+  };
+  int4 q[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      f[k] = lds_load<double>(F + (w[k] & 0x7fffu) * 8);
-      y[k] = lds_load<double>(Y + (w[k] >> 16) * 8);
-    }
-    const unsigned ng = nr >= 0 ? lds_load<unsigned>(RNG + nr * 4) : 0u;
-    if (r >= 0) {
-      if (ne <= 4) {
-        double acc = y0;
+  for (int u = 0; u < 4; ++u) q[u] = rec[u << w];
+  rec += 4 << w;
+  Seg s = fetch(q[0]);
+  double acc = 0.0;
+  for (int t = 0; t < nseg; t += 4, rec += 4 << w) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const double t = fma(-f[k], y[k], acc);
-          acc = k < ne ? t : acc;
-        }
-        if (DIV) acc = acc / lds_load<double>(D + r * 8);
-        lds_store<double>(Y + r * 8, acc);
-      } else {
-        row(r, rg);
+    for (int u = 0; u < 4; ++u) {
+      double y[4];
+      y[0] = lds_load<double>(out + (s.c0 & 0xffffu));
+      y[1] = lds_load<double>(out + (s.c0 >> 16));
+      y[2] = lds_load<double>(out + (s.c1 & 0xffffu));
+      y[3] = lds_load<double>(out + (s.c1 >> 16));
+      const Seg next = fetch(q[(u + 1) & 3]);
+      q[u] = rec[u << w];
+      const int terms = (int)(s.tag >> 16) & 7;
+      acc = ONE || (s.tag & (1u << 30)) ? s.a : acc;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc = fma(SEL && k >= terms ? 0.0 : -s.f[k], y[k], acc);
+      double v = acc;
+      if constexpr (DIV) {
+        v = quotient(acc, s.r, s.e);
+        if (divide) v = acc / lds_load<double>(D + (s.own & 0xffffu));
       }
+      if (ONE || (int)s.tag < 0) {
+        lds_store<double>(out + (s.own & 0xffffu), v);
+        if constexpr (COPY) lds_store<double>(copy + (s.own >> 16), v);
+      }
+      __asm__ volatile("" ::: "memory");
+      s = next;
     }
-    for (int q = qa + kWave; q < qb; q += kWave) {  // levels of more than 64 rows
-      const int rr = q + lane < qb ? lds_load<short>(ROWS + (q + lane) * 2) : -1;
-      if (rr >= 0) row(rr, lds_load<unsigned>(RNG + rr * 4));
-    }
-    qa = qb;
-    qb = qc;
-    qc = qd;
-    r = nr;
-    rg = ng;
-    __asm__ volatile("" ::: "memory");
   }
 }
 
-// Factorization, the IKJ form of the one-wave code, from the pattern's
-// symbolic schedule: at its level, row i takes the columns k < i it holds in
-// increasing order, replaces f_ik by f_ik / u_kk and subtracts f_ik u_kj from
-// each of its entries (i,j), j > k, that row k holds; the schedule lists, per
-// row, one header word per k (the positions of (i,k) and (k,k)) followed by
-// one word per update (the positions of (i,j) and (k,j)).  Row k is final by
-// then; row i's values are updated in place in LDS, where no other row of its
-// level reads them.  Each entry so receives its updates in increasing k.  The
-// row then stores its pivot.  A zero pivot or a non-finite factor entry
-// anywhere in the system turns M into the identity (row values 0, pivots 1).
-constexpr int kIluOpsReg = 16;  // schedule words a lane takes per pass
+// The sweep of a triangle by the first wave, between two team barriers, for a
+// sweep that divides; x is this lane's result, read at place `me`.  The
+// quotients are those of a division while |d| and the result stay within
+// 2^-400 .. 2^400 (or the result is zero): outside, the sweep is run again with
+// divisions.
+template <bool SEL, class TM>
+__device__ __forceinline__ double divided_sweep(TM& tm, const KArgs& g, const IluMw& L, unsigned reg,
+                                                bool lower, bool ok, unsigned me, bool divide) {
+  const unsigned F = reg + L.f, Y = reg + L.y, V = reg + L.v, D = F + g.noff * 8, RE = reg + L.re;
+  const int4* segs = lower ? g.seg_l : g.seg_u;
+  const int nseg = lower ? g.nseg_l : g.nseg_u, w = lower ? g.wseg_l : g.wseg_u;
+  for (;;) {
+    if (threadIdx.x < kWave) {
+      if (lower ? g.one_l : g.one_u) tri_sweep<true, SEL, false, true>(segs, nseg, w, F, V, Y, D, RE, 0, divide);
+      else tri_sweep<true, SEL, false, false>(segs, nseg, w, F, V, Y, D, RE, 0, divide);
+    }
+    tm.sync();
+    const double x = ok ? lds_load<double>(Y + me) : 0.0;
+    const bool far = !divide && x != 0.0 && !(fabs(x) > 0x1p-400 && fabs(x) < 0x1p400);
+    if (__syncthreads_or(far) == 0) return x;
+    divide = true;
+  }
+}
 
+// A pivot's reciprocal in two words (see quotient), as the sweeps read them.
+__device__ __forceinline__ void store_reciprocal(unsigned at, double d) {
+  const double r = 1.0 / d;
+  lds_store<double>(at, r);
+  lds_store<double>(at + 8, fma(-d, r, 1.0) * r);
+}
+
+// Factorization, the IKJ form of the one-wave code, from the pattern's
+// schedule: at its level, row i takes the columns k < i it holds in increasing
+// order, replaces f_ik by f_ik / u_kk and subtracts f_ik u_kj from each of its
+// entries (i,j), j > k, that row k holds.  Row k is final by then; row i's
+// values are updated in place in LDS, where no other row of its level reads
+// them.  Each entry so receives its updates in increasing k.  The row then
+// stores its pivot's reciprocal.  Lane q takes the q-th row in lower order, so
+// that one wave or two work on a level and the others only meet its barrier
+// (with row i on lane i, up to 16 waves had a row each); a pivot and four of
+// its updates are one group of schedule words, whose LDS reads go out together.
+// 204 us per system of 992 rows with every update waiting for its own reads,
+// now 121 (reading the system included).  A zero pivot or a non-finite factor
+// entry anywhere in the system turns M into the identity (row values 0, pivots
+// 1).
 template <class TM, class RW>
 __device__ void ilu_setup_mw(TM& tm, const RW& A, const KArgs& g) {
   static_assert(RW::R == 1 && RW::TEAM > kWave, "multi-wave ILU(0): one row per lane");
   constexpr int NZ = RW::NZ;
   const IluMw L = ilu_mw_layout(g.n, g.nnz);
   const unsigned reg = lds_addr(tm.bj_region(g));
-  const unsigned F = reg + L.f, D = reg + L.d;
-  sweep_lists_load(tm, g, reg, L);
+  const unsigned F = reg + L.f, D = F + g.noff * 8, RE = reg + L.re;
+  tri_cells(tm, g, reg, L);
   const bool ok = A.ok[0];
   int i = ok ? A.row[0] : 0;
   // opaque once per system: everything below derives from the pattern, and
   // would otherwise be loaded or formed once per kernel and pin registers
   // through the whole solve
   __asm__ volatile("" : "+v"(i));
-  const int lv = ok ? g.lev[i] : 0;
-  const int fb = g.fmt == 0 ? A.w[0] : g.row_ptr[i];  // CSR position of register slot 0
-  const unsigned fr = F + fb * 8;
-  const int o0 = g.ilu_ptr[i], o1 = ok ? g.ilu_ptr[i + 1] : o0;
-  // Shapes of up to 16 slots load the row's first words before the level loop
+  const int e0 = g.fmt == 0 ? A.w[0] : g.row_ptr[i];  // CSR position of register slot 0
+  tm.place = (unsigned)g.tri_place[i];
+  // the lane's row in lower order (ok also tells whether there is one)
+  const int lv = ok ? g.lev[i] : -1;
+  const unsigned up = (unsigned)g.tri_up[i];
+  // Shapes of up to 16 slots load the row's first groups before the level loop
   // (all lanes at once); wider ones, short of registers, load them when the
   // row's level comes.
-  constexpr bool kEarly = NZ <= 16;
-  unsigned w[kIluOpsReg];
+  constexpr int kEarly = NZ <= 16 ? 4 : 0;
+  const int o0 = g.ilu_ptr[i], o1 = ok ? g.ilu_ptr[i + 1] : o0;
+  unsigned w[kEarly > 0 ? kEarly : 1][5];
 #pragma unroll
-  for (int q = 0; q < kIluOpsReg; ++q)
-    w[q] = kEarly && o0 + q < o1 ? (unsigned)g.ilu_ops[o0 + q] : 0u;
-  // publish the row's values
+  for (int q = 0; q < kEarly; ++q)
+#pragma unroll
+    for (int u = 0; u < 5; ++u) w[q][u] = o0 + 5 * q < o1 ? (unsigned)g.ilu_ops[o0 + 5 * q + u] : 0u;
+  // publish row i's values (a row without a stored diagonal has pivot 0)
   if (ok) {
+    if (A.dslot[0] < 0) lds_store<double>(D + (tm.place >> 16) * 8, 0.0);
 #pragma unroll
     for (int s = 0; s < NZ; ++s)
-      if (A.real(0, s)) lds_store<double>(fr + s * 8, A.a[0][s]);
+      if (A.real(0, s)) lds_store<double>(F + g.tri_pos[e0 + s] * 8, A.a[0][s]);
   }
   tm.sync();
-  const int mine = ok ? (lv & 0xffff) : -1;
-  for (int l = 0; l < g.nlev_l; ++l) {
-    if (mine == l) {
-      double lik = 0.0;
-      for (int b0 = o0; b0 < o1; b0 += kIluOpsReg) {
-        if (kEarly && b0 != o0) {
+  double lik = 0.0;
+  auto group = [&](const unsigned (&v)[5]) {
+    const bool head = v[0] >> 31;
+    const unsigned aik = F + (v[0] & 0x7fffu) * 8, kk = (v[0] >> 15) & 0xffffu;
+    double a = 0.0, d = 1.0, r = 1.0, e = 0.0, x[4], y[4];
+    if (head) {
+      a = lds_load<double>(aik);
+      d = lds_load<double>(F + kk * 8);
+      r = lds_load<double>(RE + (kk - g.noff) * 16);
+      e = lds_load<double>(RE + (kk - g.noff) * 16 + 8);
+    }
 #pragma unroll
-          for (int q = 0; q < kIluOpsReg; ++q)
-            w[q] = b0 + q < o1 ? (unsigned)g.ilu_ops[b0 + q] : 0u;
-        }
+    for (int q = 0; q < 4; ++q) {
+      x[q] = lds_load<double>(F + (v[1 + q] & 0xffffu) * 8);
+      y[q] = lds_load<double>(F + (v[1 + q] >> 16) * 8);
+    }
+    if (head) {
+      lik = quotient(a, r, e);
+      if (!quotient_safe(a, d)) lik = a / d;
+      lds_store<double>(aik, lik);
+    }
 #pragma unroll
-        for (int q = 0; q < kIluOpsReg; ++q) {
-          if (b0 + q < o1) {
-            const unsigned op = kEarly ? w[q] : (unsigned)g.ilu_ops[b0 + q];
-            if (op >> 31) {
-              const unsigned aik = F + (op & 0x7fffu) * 8, akk = F + ((op >> 15) & 0x7fffu) * 8;
-              lik = lds_load<double>(aik) / lds_load<double>(akk);
-              lds_store<double>(aik, lik);
-            } else {
-              const unsigned aij = F + (op & 0xffffu) * 8, akj = F + (op >> 16) * 8;
-              lds_store<double>(aij, fma(-lik, lds_load<double>(akj), lds_load<double>(aij)));
-            }
-          }
-        }
+    for (int q = 0; q < 4; ++q) lds_store<double>(F + (v[1 + q] & 0xffffu) * 8, fma(-lik, y[q], x[q]));
+  };
+  for (int l = 0; l < g.nlev; ++l) {
+    if (lv == l) {
+#pragma unroll
+      for (int q = 0; q < kEarly; ++q)
+        if (o0 + 5 * q < o1) group(w[q]);
+      for (int o = o0 + 5 * kEarly; o < o1; o += 5) {
+        unsigned v[5];
+#pragma unroll
+        for (int u = 0; u < 5; ++u) v[u] = (unsigned)g.ilu_ops[o + u];
+        group(v);
       }
-      lds_store<double>(D + i * 8, A.dslot[0] >= 0 ? lds_load<double>(fr + A.dslot[0] * 8) : 0.0);
+      store_reciprocal(RE + up * 16, lds_load<double>(D + up * 8));
     }
     tm.sync();
   }
-  bool bad = false;
+  bool bad = false, wide = false;
   if (ok) {
-    bad = lds_load<double>(D + i * 8) == 0.0;
+    const double d = lds_load<double>(D + (tm.place >> 16) * 8);
+    double sum = 0.0;  // of 0 * entry: not a number when one is not finite
 #pragma unroll
     for (int s = 0; s < NZ; ++s)
-      bad = bad || (A.real(0, s) && !__builtin_isfinite(lds_load<double>(fr + s * 8)));
+      if (A.real(0, s)) sum = fma(lds_load<double>(F + g.tri_pos[e0 + s] * 8), 0.0, sum);
+    bad = d == 0.0 || !__builtin_isfinite(sum);
+    wide = !quotient_safe(0.0, d);
   }
+  tm.divide = __syncthreads_or(wide) != 0;
   if (__syncthreads_or(bad)) {
+    tm.divide = false;
     if (ok) {
 #pragma unroll
       for (int s = 0; s < NZ; ++s)
-        if (A.real(0, s)) lds_store<double>(fr + s * 8, 0.0);
-      lds_store<double>(D + i * 8, 1.0);
+        if (A.real(0, s)) lds_store<double>(F + g.tri_pos[e0 + s] * 8, 0.0);
+      lds_store<double>(D + (tm.place >> 16) * 8, 1.0);
+      store_reciprocal(RE + (tm.place >> 16) * 16, 1.0);
     }
     tm.sync();
   }
@@ -653,15 +683,15 @@ __device__ __forceinline__ void ilu_apply_mw(TM& tm, const RW& A, const KArgs& g
                                              const T (&v)[RW::R], T (&z)[RW::R]) {
   const IluMw L = ilu_mw_layout(g.n, g.nnz);
   const unsigned reg = lds_addr(tm.bj_region(g));
-  const unsigned me = reg + L.y + (unsigned)A.row[0] * 8;
-  if (A.ok[0]) lds_store<double>(me, (double)v[0]);
+  const unsigned F = reg + L.f, Y = reg + L.y, V = reg + L.v;
+  const bool ok = A.ok[0];
+  if (ok) lds_store<double>(Y + (tm.place & 0xffffu) * 8, (double)v[0]);
   tm.sync();
   if (threadIdx.x < kWave) {
-    tri_sweep<true, false>(g, reg, L);
-    tri_sweep<false, true>(g, reg, L);
+    if (g.one_l) tri_sweep<false, false, true, true>(g.seg_l, g.nseg_l, g.wseg_l, F, Y, Y, 0, 0, V, false);
+    else tri_sweep<false, false, true, false>(g.seg_l, g.nseg_l, g.wseg_l, F, Y, Y, 0, 0, V, false);
   }
-  tm.sync();
-  z[0] = A.ok[0] ? (T)lds_load<double>(me) : (T)0;
+  z[0] = (T)divided_sweep<false>(tm, g, L, reg, false, ok, (tm.place >> 16) * 8, tm.divide);
 }
 
 // z = M v: block Jacobi or ILU(0) in their instances, else the diagonal d
@@ -1118,19 +1148,23 @@ __device__ __forceinline__ void trsv_system_mw(TM& tm, RW& A, const KArgs& g) {
   constexpr int NZ = RW::NZ;
   const IluMw L = ilu_mw_layout(g.n, g.nnz);
   const unsigned reg = lds_addr(tm.bj_region(g));
-  sweep_lists_load(tm, g, reg, L);
+  const unsigned F = reg + L.f, D = F + g.noff * 8, RE = reg + L.re, V = reg + L.v;
+  tri_cells(tm, g, reg, L);
   const bool ok = A.ok[0];
   int i = ok ? A.row[0] : 0;
   __asm__ volatile("" : "+v"(i));  // per system: keeps the row's addresses out of the kernel-wide registers
-  const unsigned fr = reg + L.f + (unsigned)(g.fmt == 0 ? A.w[0] : g.row_ptr[i]) * 8;
-  const unsigned me = reg + L.y + (unsigned)i * 8;
+  const int e0 = g.fmt == 0 ? A.w[0] : g.row_ptr[i];  // CSR position of register slot 0
+  const int place = g.tri_place[i];
+  const unsigned me = (unsigned)(LOWER ? place & 0xffff : place >> 16) * 8;
   const double tii = ok ? A.dval[0] : 1.0;
   if (ok) {
+    // the triangle's entries off the diagonal; the diagonal in the sweep's order
 #pragma unroll
     for (int s = 0; s < NZ; ++s)
-      if (A.real(0, s)) lds_store<double>(fr + s * 8, A.a[0][s]);
-    lds_store<double>(reg + L.d + (unsigned)i * 8, tii);
-    lds_store<double>(me, A.bval[0]);
+      if (A.real(0, s) && s != A.dslot[0]) lds_store<double>(F + g.tri_pos[e0 + s] * 8, A.a[0][s]);
+    lds_store<double>(D + me, tii);
+    store_reciprocal(RE + me * 2, tii);
+    lds_store<double>(V + me, A.bval[0]);
   }
 #pragma unroll
   for (int s = 0; s < NZ; ++s) {
@@ -1141,6 +1175,7 @@ __device__ __forceinline__ void trsv_system_mw(TM& tm, RW& A, const KArgs& g) {
   tm.sum(q);  // also makes the stores above visible to the team
   const double bn = sqrt(q[0]);
   const bool zero_diag = __syncthreads_or(ok && tii == 0.0) != 0;
+  const bool wide = __syncthreads_or(!quotient_safe(0.0, tii)) != 0;
   int stt = tm.live ? ST_CONVERGED : ST_IDLE;
   if (tm.live && !finite(bn)) {
     stt = ST_NONFINITE;
@@ -1148,9 +1183,7 @@ __device__ __forceinline__ void trsv_system_mw(TM& tm, RW& A, const KArgs& g) {
     if (tm.live && bn != 0.0) stt = ST_BREAKDOWN;
     x[0] = 0.0;
   } else {
-    if (threadIdx.x < kWave) tri_sweep<LOWER, true>(g, reg, L);
-    tm.sync();
-    x[0] = ok ? lds_load<double>(me) : 0.0;
+    x[0] = divided_sweep<true>(tm, g, L, reg, LOWER, ok, me, wide);
     const bool nf = __syncthreads_or(ok && !finite(x[0])) != 0;
     if (tm.live && nf) stt = ST_NONFINITE;
   }
@@ -1684,14 +1717,25 @@ constexpr int kRegBlock = S::TEAM == kWave && S::R == 1 ? pf_chunks(S::NZ) : 0;
 // ILU(0) on one-wave teams: the dense factors (about 25 KB of LDS per wave
 // for 54 rows) leave room for fewer than two waves per SIMD, so the register
 // budget is that of two (no spills) rather than three.
+// Multi-wave ones: the sweep's records and values one segment ahead take about
+// 40 registers, which would cost a resident wave per SIMD where the rows are
+// short; held to the count that the rows alone allow, the compiler parks a few
+// of the row's own across the sweep instead (1024 triangular solves of 256
+// rows: 34.4 us without the limit, 24.6 with it; 700 systems of 182 rows with
+// ILU(0): 325 and 191 us).
+template <class S, bool TRSV>
+constexpr int kTriOcc = S::TEAM > kWave && S::TEAM < 1024 && S::NZ <= (TRSV ? 32 : 16)
+                            ? (S::NZ <= (TRSV ? 16 : 8) ? 4 : 3)
+                            : S::OCC_MIXED;
+
 template <class S, bool MIXED, int PK = kPkScalar>
-__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu((MIXED || PK == kPkIlu) ? S::OCC_MIXED : S::OCC))) void k_bicgstab(const KArgs g) {
+__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(PK == kPkIlu ? kTriOcc<S, false> : MIXED ? S::OCC_MIXED : S::OCC))) void k_bicgstab(const KArgs g) {
   BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (PK == kPkIlu ? kRegBlock<S> : 0),
                      (bicgstab_system<MIXED, PK>(tm, A, ga)))
 }
 
 template <class S, bool LOWER>
-__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC_MIXED))) void k_trsv(const KArgs g) {
+__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(kTriOcc<S, true>))) void k_trsv(const KArgs g) {
   BS_PERSISTENT_LOOP(false, kRegBlock<S>, (trsv_system<LOWER>(tm, A, ga)))
 }
 
