@@ -120,6 +120,8 @@ int hip_fail(hipError_t e, const char* what) {
   return BS_ERR_HIP;
 }
 
+constexpr int kLdsPerCu = 160 * 1024;
+
 // The multi-wave triangular schedules hold rows and entries in 16-bit words.
 constexpr int kTriRows = 1024;
 
@@ -255,6 +257,21 @@ void tri_schedule(bs_pattern_s& p) {
   }
 }
 
+const bs::KernelEntry* find_kernel(int variant, int team, int r, int nz_min);
+
+// Whether some multi-wave shape can take the pattern for ILU(0) or BatchTrsv:
+// the schedule of a pattern that none holds would only cost its creation time
+// (a dense one of 150 rows: 2 ms).
+bool takes_tri_schedule(const bs_pattern_s& p) {
+  if (p.n > kTriRows || p.nnz >= (1 << 15) || bs::tri_limit_bytes(p.n, p.nnz) > kLdsPerCu)
+    return false;
+  for (int t = 2 * bs::kWave; t <= 1024; t *= 2)
+    if (t >= p.n && (find_kernel(bs::V_BICGSTAB_ILU, t, 1, std::max(p.max_row, 1)) ||
+                     find_kernel(bs::V_TRSV_LOWER, t, 1, std::max(p.max_row, 1))))
+      return true;
+  return false;
+}
+
 // Derived per-row data shared by the CSR and ELL forms.
 void derive(bs_pattern_s& p) {
   const int n = p.n;
@@ -273,7 +290,7 @@ void derive(bs_pattern_s& p) {
   for (int s = 0; s < p.width; ++s)
     for (int i = 0; i < n; ++i)
       if (s < p.row_len[i]) p.slot_col[(size_t)s * n + i] = p.col[p.row_ptr[i] + s];
-  if (n <= kTriRows && p.nnz < (1 << 15)) tri_schedule(p);
+  if (takes_tri_schedule(p)) tri_schedule(p);
   // The one-wave schedule: rows and columns as 64-bit masks.
   p.ilu64.clear();
   if (n <= bs::kWave) {
@@ -472,7 +489,6 @@ int block_of(const bs_options* o, int precond = BS_PREC_BLOCK_JACOBI) {
 // Staging of CSR values through LDS is used while a workgroup's staging area
 // stays within this budget.
 constexpr int kStageBudget = 48 * 1024;
-constexpr int kLdsPerCu = 160 * 1024;
 
 struct Plan {
   bs_plan_info info;
