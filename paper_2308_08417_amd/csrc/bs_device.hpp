@@ -304,6 +304,10 @@ struct Team {
   // Whether any team of this wave satisfies p.  For multi-wave teams every
   // wave sees the same (team-uniform) predicate.
   __device__ __forceinline__ bool any(bool p) const { return wave_any(p); }
+  __device__ __forceinline__ void any2(bool p, bool q, bool& any_p, bool& any_q) const {
+    any_p = wave_any(p);
+    any_q = wave_any(q);
+  }
 
 };
 

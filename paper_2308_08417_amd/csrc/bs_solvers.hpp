@@ -925,7 +925,9 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
         st = ST_MAX_ITER;
       }
     }
-    if (tm.any(need_chk)) {
+    bool any_chk, any_run;
+    tm.any2(need_chk, st == ST_RUNNING, any_chk, any_run);
+    if (any_chk) {
       // ---- true residual (plain) / outer refinement step (mixed), FP64
       double t[R], pr[R], q[1];
       A.template spmv<0>(tm, A.a, P.x, t);
@@ -968,7 +970,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       }
       continue;
     }
-    if (!tm.any(st == ST_RUNNING)) break;
+    if (!any_run) break;
 
     // ---- one BiCGSTAB iteration; committed for teams still running
     bool go = st == ST_RUNNING;
@@ -1239,7 +1241,9 @@ __device__ __forceinline__ void cg_system(TM& tm, RW& A, const KArgs& g) {
       else if (rsq <= lim2) { if (rtrue) st = ST_CONVERGED; else need_chk = true; }
       else if (k >= g.max_iter) st = ST_MAX_ITER;
     }
-    if (tm.any(need_chk)) {
+    bool any_chk, any_run;
+    tm.any2(need_chk, st == ST_RUNNING, any_chk, any_run);
+    if (any_chk) {
       double t[R], rc[R], zc[R], p0[R], p1[R], q[2];
       A.template spmv<0>(tm, A.a, P.x, t);
 #pragma unroll
@@ -1267,7 +1271,7 @@ __device__ __forceinline__ void cg_system(TM& tm, RW& A, const KArgs& g) {
       }
       continue;
     }
-    if (!tm.any(st == ST_RUNNING)) break;
+    if (!any_run) break;
     bool go = st == ST_RUNNING;
     if (go && rho == 0.0) { st = ST_BREAKDOWN; go = false; }
     double t[R];
