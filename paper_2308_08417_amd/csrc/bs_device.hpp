@@ -154,6 +154,14 @@ __device__ __forceinline__ void wave_sums(T (&v)[K]) {
   }
 }
 
+// A value all lanes of the wave hold, in scalar registers.
+__device__ __forceinline__ double wave_uniform(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
 __device__ __forceinline__ int row16_max(int v) {
   v = max(v, dpp<0xB1>(v));
   v = max(v, dpp<0x4E>(v));
@@ -308,6 +316,7 @@ struct Team {
     any_p = wave_any(p);
     any_q = wave_any(q);
   }
+  __device__ __forceinline__ unsigned lean_cell(int, int) const { return 0; }
 
 };
 

@@ -816,12 +816,34 @@ __device__ __forceinline__ void prologue(TM& tm, RW& A, const KArgs& g, Prologue
 // FP32 and solve for a correction to the FP64 x, scaled by 1/||r||; the "true
 // residual confirmation" becomes the FP64 outer refinement step r = b - A x,
 // which also ends the inner solve when it meets inner_tol or breaks down.
-template <bool MIXED, int PK, class TM, class RW>
+// Vectors of the lean form (see kVarLean), in the lane's LDS cells.
+constexpr int kLeanX = 0, kLeanB = 1, kLeanD = 2, kLeanRh = 3, kLeanVectors = 4;
+
+template <bool MIXED, int PK, bool LEAN = false, class TM, class RW>
 __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
   using T = typename std::conditional<MIXED, float, double>::type;
   Prologue<RW::R> P;
   prologue<PK>(tm, A, g, P);
   constexpr int R = RW::R;
+  static_assert(!LEAN || (!MIXED && PK == kPkScalar), "lean: FP64, scalar Jacobi or none");
+  // LEAN: vectors kept in the lane's own LDS cells
+  auto keep = [&](int q, const double(&u)[R]) {
+    if constexpr (LEAN) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) lds_store<double>(tm.lean_cell(q, i), u[i]);
+    }
+  };
+  auto kept = [&](int q, double(&u)[R]) {
+    if constexpr (LEAN) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) u[i] = lds_load<double>(tm.lean_cell(q, i));
+    }
+  };
+  // LEAN: a lane-uniform value moved to scalar registers
+  auto uni = [&](auto u) {
+    if constexpr (LEAN) return wave_uniform(u);
+    else return u;
+  };
 
   // FP32 copy of the rows and of the Jacobi diagonal for the inner solve.
   using AT = typename std::conditional<MIXED, float, double>::type;
@@ -848,9 +870,9 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     q2[1] = sum_rows(p1);
     tm.sum(q2);
   }
-  const double bn = sqrt(q2[0]);
-  double rn = sqrt(q2[1]);  // FP64 norm of the outer (or only) residual
-  const double lim = stop_limit(g, bn);
+  const double bn = uni(sqrt(q2[0]));
+  double rn = uni(sqrt(q2[1]));  // FP64 norm of the outer (or only) residual
+  const double lim = uni(stop_limit(g, bn));
   int st = tm.live ? ST_RUNNING : ST_IDLE;
   bool rtrue = true;
   if (st == ST_RUNNING) {
@@ -883,6 +905,10 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     rho0 = alpha = omega = (T)1;
   };
   restart(rn);
+  keep(kLeanX, P.x);
+  keep(kLeanB, P.b);
+  keep(kLeanD, P.d);
+  if constexpr (LEAN) keep(kLeanRh, rh);
   if constexpr (MIXED) {
     T q[1];
     T pr[R];
@@ -908,7 +934,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
   // The recurrence tests compare squared norms (no square root per test);
   // the true-residual confirmation below compares the norm itself.
   T ilim = inner_lim();
-  T ilim2 = ilim * ilim;
+  T ilim2 = uni(ilim * ilim);
   bool inner_end = false;  // MIXED: inner solve ended (met inner tol or broke down)
 
   for (;;) {
@@ -930,7 +956,9 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     if (any_chk) {
       // ---- true residual (plain) / outer refinement step (mixed), FP64
       double t[R], pr[R], q[1];
+      kept(kLeanX, P.x);
       A.template spmv<0>(tm, A.a, P.x, t);
+      kept(kLeanB, P.b);
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         const double e = P.b[i] - t[i];
@@ -940,7 +968,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       q[0] = sum_rows(pr);
       tm.sum(q);
       if (need_chk) {
-        const double rnc = sqrt(q[0]);
+        const double rnc = uni(sqrt(q[0]));
         rtrue = true;
         if constexpr (MIXED) outer += 1;
         const bool stagnant = MIXED && !(rnc < rn_prev);
@@ -952,6 +980,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
         else if (stagnant) st = ST_BREAKDOWN;
         else {
           restart(rnc);
+          if constexpr (LEAN) keep(kLeanRh, rh);
           inner_end = false;
           ilim = inner_lim();
           ilim2 = ilim * ilim;
@@ -986,6 +1015,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     }
     const T beta = (rho * alpha) / (rho0 * omega);
     T ph[R], s[R], sh[R], t[R];
+    if constexpr (LEAN) kept(kLeanD, d_in);
 #pragma unroll
     for (int i = 0; i < R; ++i) p[i] = r[i] + beta * (p[i] - omega * v[i]);
     precond<PK>(tm, A, g, d_in, p, ph);
@@ -993,6 +1023,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     T q1[1];
     {
       T pr[R];
+      if constexpr (LEAN) kept(kLeanRh, rh);
 #pragma unroll
       for (int i = 0; i < R; ++i) pr[i] = rh[i] * v[i];
       q1[0] = sum_rows(pr);
@@ -1003,7 +1034,8 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       if (!finite((double)sigma)) { if (MIXED) inner_end = true; else st = ST_NONFINITE; go = false; }
       else if (sigma == (T)0) { if (MIXED) inner_end = true; else st = ST_BREAKDOWN; go = false; }
     }
-    const T al = rho / sigma;
+    const T al = uni(rho / sigma);
+    if constexpr (LEAN) kept(kLeanD, d_in);
 #pragma unroll
     for (int i = 0; i < R; ++i) s[i] = r[i] - al * v[i];
     precond<PK>(tm, A, g, d_in, s, sh);
@@ -1029,17 +1061,29 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       }
     }
     const double sal = scale * (double)al;
+    if constexpr (LEAN) {
+      // z = M p and M s are formed again rather than held through the products
+      kept(kLeanD, d_in);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        __asm__ volatile("" : "+v"(p[i]), "+v"(s[i]));
+        ph[i] = d_in[i] * p[i];
+        sh[i] = d_in[i] * s[i];
+      }
+      if (half || go) kept(kLeanX, P.x);
+    }
     if (half) {
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         P.x[i] = fma(sal, (double)ph[i], P.x[i]);
         r[i] = s[i];
       }
+      keep(kLeanX, P.x);
       rtrue = false;
       rr_in = ss;
       go = false;
     }
-    const T om = (tt == (T)0) ? (T)0 : ts / tt;
+    const T om = uni((tt == (T)0) ? (T)0 : ts / tt);
     if (go) {
       const double som = scale * (double)om;
 #pragma unroll
@@ -1047,6 +1091,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
         P.x[i] = fma(som, (double)sh[i], fma(sal, (double)ph[i], P.x[i]));
         r[i] = s[i] - om * t[i];
       }
+      keep(kLeanX, P.x);
       rtrue = false;
       rho0 = rho;
       alpha = al;
@@ -1055,6 +1100,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
     T q4[2];
     {
       T p0[R], p1[R];
+      if constexpr (LEAN) kept(kLeanRh, rh);
 #pragma unroll
       for (int i = 0; i < R; ++i) { p0[i] = r[i] * r[i]; p1[i] = rh[i] * r[i]; }
       q4[0] = sum_rows(p0);
@@ -1069,6 +1115,8 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       }
     }
   }
+  kept(kLeanX, P.x);
+  kept(kLeanB, P.b);
   finish(tm, A, g, P.b, P.x, st, k, outer, bn, rn, st == ST_CONVERGED || st == ST_IDLE);
 }
 

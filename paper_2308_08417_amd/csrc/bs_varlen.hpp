@@ -95,7 +95,7 @@ struct VarTeam {
   int64_t sys, row0;
   bool live;
   char* lds;
-  double* red;         // cross-wave reduction slots
+  int wave;            // of the workgroup
   int phase;
   int turn;            // set of predicate words in use
 
@@ -106,7 +106,7 @@ struct VarTeam {
     wpt = t / kWave;
     lgw = __builtin_ctz((unsigned)wpt);
     lds = smem;
-    red = reinterpret_cast<double*>(smem + 2 * var_buf_bytes<VS>());
+    wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   }
 
   // Single-wave teams: a wave's LDS operations complete in issue order, so a
@@ -126,6 +126,12 @@ struct VarTeam {
     return reinterpret_cast<double*>(lds + var_lds_bytes<VS>()) + (size_t)tix * T * VS::R * (g.block + 1);
   }
   __device__ __forceinline__ int bj_rows() const { return T * VS::R; }
+  // This lane's cell of vector q, row slot r, of the vectors a lean solver keeps
+  // in LDS.
+  __device__ __forceinline__ unsigned lean_cell(int q, int r) const {
+    return lds_addr(lds) + var_lds_bytes<VS>() + (unsigned)((q * VS::R + r) * VS::WG) * 8 +
+           (unsigned)wave * (kWave * 8) + lane_id() * 8;
+  }
 
   // Whether any team that advances with this one satisfies p (q).  A team's
   // lanes agree, so a workgroup that holds one team asks its own wave, as a
@@ -135,16 +141,21 @@ struct VarTeam {
   // without; 4100 of 257 to 512 rows, two teams each: 770 and 624 us.)  The sets of words alternate: one is written again
   // only after the barrier of the other.
   __device__ __forceinline__ void any2(bool p, bool q, bool& any_p, bool& any_q) {
+    any2_as<false>(p, q, any_p, any_q);
+  }
+  template <bool FORM>  // see sum_as
+  __device__ __forceinline__ void any2_as(bool p, bool q, bool& any_p, bool& any_q) {
     if (wpt == 1 || wpt == VS::WAVES) {
       any_p = wave_any(p);
       any_q = wave_any(q);
       return;
     }
     const unsigned words = lds_addr(lds) + var_lds_bytes<VS>() - 2 * VS::WAVES * 4 + turn * (VS::WAVES * 4);
-    if ((threadIdx.x & 63) == 0)
-      lds_store<int>(words + (threadIdx.x >> 6) * 4, (p ? 1 : 0) | (q ? 2 : 0));
+    unsigned l = lane_id();
+    if constexpr (FORM) __asm__ volatile("" : "+v"(l));
+    if (l == 0) lds_store<int>(words + wave * 4, (p ? 1 : 0) | (q ? 2 : 0));
     __syncthreads();
-    const int w = lds_load<int>(words + (threadIdx.x & (VS::WAVES - 1)) * 4);
+    const int w = lds_load<int>(words + (l & (VS::WAVES - 1)) * 4);
     any_p = wave_any((w & 1) != 0);
     any_q = wave_any((w & 2) != 0);
     turn ^= 1;
@@ -156,28 +167,49 @@ struct VarTeam {
   }
 
   template <class V, int K>
-  __device__ __forceinline__ void sum(V (&v)[K]) {
+  __device__ __forceinline__ void sum(V (&v)[K]) { sum_as<false>(v); }
+
+  // FORM: the lane's addresses are formed at each sum; kept, they take registers
+  // through the whole solve.
+  template <bool FORM, class V, int K>
+  __device__ __forceinline__ void sum_as(V (&v)[K]) {
     static_assert(K <= kMaxFused && K * 16 <= 64, "too many fused values");
     wave_sums(v);
     if (wpt > 1) {
-      double* buf = red + phase * (kMaxFused * VS::WAVES);
-      const int w = threadIdx.x >> 6;
-      if ((threadIdx.x & 63) == 0) {
+      unsigned l = lane_id();
+      if constexpr (FORM) __asm__ volatile("" : "+v"(l));
+      const unsigned buf = lds_addr(lds) + 2 * var_buf_bytes<VS>() + phase * (kMaxFused * VS::WAVES * 8);
+      if (l == 0) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) buf[k * VS::WAVES + w] = (double)v[k];
+        for (int k = 0; k < K; ++k) lds_store<double>(buf + (k * VS::WAVES + wave) * 8, (double)v[k]);
       }
       __syncthreads();
       // lane l reads value l / wpt of its team's wave (l mod wpt); a butterfly
       // over aligned groups of wpt lanes leaves value k's team total in lanes
       // k*wpt .. k*wpt+wpt-1 (wpt is a power of two from 2 to 16, uniform over
       // the workgroup, and K * wpt <= 64)
-      const int l = threadIdx.x & 63;
-      const int vi = (l >> lgw) < K ? (l >> lgw) : 0;
-      const double t = group_sum(buf[vi * VS::WAVES + tix * wpt + (l & (wpt - 1))], wpt);
+      const unsigned vi = (l >> lgw) < K ? (l >> lgw) : 0;
+      const double t = group_sum(
+          lds_load<double>(buf + (vi * VS::WAVES + (wave & -wpt) + (l & (wpt - 1))) * 8), wpt);
 #pragma unroll
       for (int k = 0; k < K; ++k) v[k] = (V)rdlane(t, k * wpt);
       phase ^= 1;
     }
+  }
+};
+
+// The team of kernels short of registers (see kVarOcc).
+template <class VS>
+struct ShortTeam : VarTeam<VS> {
+  template <class V, int K>
+  __device__ __forceinline__ void sum(V (&v)[K]) { this->template sum_as<true>(v); }
+  __device__ __forceinline__ void any2(bool p, bool q, bool& any_p, bool& any_q) {
+    this->template any2_as<true>(p, q, any_p, any_q);
+  }
+  __device__ __forceinline__ bool any(bool p) {
+    bool r, unused;
+    any2(p, false, r, unused);
+    return r;
   }
 };
 
@@ -196,6 +228,8 @@ template <class VS, int NZ_, int SRC = kSrcCsr, bool MX = false>
 struct VarRows {
   static constexpr int R = VS::R, NZ = NZ_, ROWS = VS::ROWS;
   static constexpr int OCC = VS::OCC;  // waves per SIMD the allocator is held to
+  // short rows of 512 lanes x 2 rows: see kVarLean
+  static constexpr bool SHORT = !MX && VS::WG == 512 && R == 2 && NZ <= 10;
   static constexpr unsigned kBuf = var_buf_bytes<VS>();
   static constexpr unsigned kElem = MX ? 4 : 8;  // bytes between elements in c and vrow
   double a[R][NZ];
@@ -366,8 +400,15 @@ struct VarRows {
       }
     };
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (ok[r]) lds_store<V>(at(vrow[r]) + off, v[r]);
+    for (int r = 0; r < R; ++r) {
+      unsigned x = vrow[r];
+      if constexpr (SHORT) {  // formed from the first row's: one register less
+        x = vrow[0];
+        if (r > 0) __asm__ volatile("" : "+v"(x));
+        x += (unsigned)(r * tm.T) * kElem;
+      }
+      if (ok[r]) lds_store<V>(at(x) + off, v[r]);
+    }
     if constexpr (MX && sizeof(V) == 4) {
       if (tm.lane == 0) lds_store<float>(zero + off, 0.0f);
     }
@@ -404,6 +445,7 @@ struct VarRowsS {
   // without the rows in registers two workgroups fit one CU: four waves per
   // SIMD (128 registers a lane) for 512 lanes, two (256) for 256 lanes x 4 rows
   static constexpr int OCC = VS::WG >= 512 ? 4 : 2;
+  static constexpr bool SHORT = false;
   static constexpr unsigned kBuf = var_buf_bytes<VS>();
   double a[R][NZ];  // not read: the products take the values from memory
   unsigned vrow[R];
@@ -565,13 +607,30 @@ struct VarRowsS {
 constexpr int kMaxClasses = 8;
 __global__ void k_varlen_reset(int* counter);
 
+// Short rows on 512 lanes x 2 rows (up to 10 slots, FP64, scalar Jacobi or
+// none): held to four waves per SIMD, so that two workgroups fit one compute
+// unit and one loads or waits at a barrier while the other computes.  CG fits
+// these 128 registers as it is.  BiCGSTAB took 180 (and held to 128 with
+// nothing else changed spilled 53 of them inside its loop, at twice the time):
+// lean, it keeps x, b, the Jacobi diagonal and r^ in the lane's own LDS cells,
+// the team's scalars in scalar registers, and forms M p and M s a second time
+// for the update of x.  8200 systems of 512 to 1024 rows: 2140 us with one
+// workgroup per compute unit, 1456 with two.  From 12 slots on the rows alone
+// leave no room.
+template <class RowsT, int SOLVER, bool MIXED, bool BJ>
+constexpr bool kVarLean = RowsT::SHORT && SOLVER == 1 && !MIXED && !BJ;
+template <class RowsT, int SOLVER, bool MIXED, bool BJ>
+constexpr int kVarOcc = RowsT::SHORT && !MIXED && !BJ ? 4 : RowsT::OCC;
+
 // RowsT: VarRows<VS, NZ, SRC> (rows in registers) or VarRowsS<VS, SRC>.
 template <class VS, class RowsT, int SOLVER, bool MIXED, bool BJ = false>
-__global__ __launch_bounds__(VS::WG) __attribute__((amdgpu_waves_per_eu(RowsT::OCC)))
+__global__ __launch_bounds__(VS::WG) __attribute__((amdgpu_waves_per_eu((kVarOcc<RowsT, SOLVER, MIXED, BJ>))))
 void k_varlen(const VArgs va) {
   static_assert(!(MIXED && BJ), "the mixed kernels' per-team blocks carry no block Jacobi");
   // buffers and reduction slots, then (BJ) the block-Jacobi region of the largest block
-  __shared__ __align__(16) char smem[var_lds_bytes<VS>() + (BJ ? bj_bytes(VS::ROWS, kMaxBlock) : 0)];
+  constexpr bool LEAN = kVarLean<RowsT, SOLVER, MIXED, BJ>;
+  __shared__ __align__(16) char smem[var_lds_bytes<VS>() + (BJ ? bj_bytes(VS::ROWS, kMaxBlock) : 0) +
+                                     (LEAN ? kLeanVectors * VS::ROWS * 8 : 0)];
   __shared__ int task_sh;
   const unsigned lds_base = lds_addr(smem);
   constexpr unsigned kBuf = var_buf_bytes<VS>();
@@ -579,7 +638,7 @@ void k_varlen(const VArgs va) {
     const int b = threadIdx.x / VS::MAXT, t = threadIdx.x % VS::MAXT;
     lds_store<double>(lds_base + b * kBuf + (VS::ROWS + t) * 8, 0.0);
   }
-  VarTeam<VS> tm;
+  typename std::conditional<RowsT::SHORT && !MIXED && !BJ, ShortTeam<VS>, VarTeam<VS>>::type tm;
   tm.phase = 0;
   tm.turn = 0;
   for (;;) {
@@ -602,7 +661,7 @@ void k_varlen(const VArgs va) {
     RowsT A;
     A.load(tm, a, lds_base);
     if constexpr (SOLVER == 0) cg_system<BJ ? kPkBlock : kPkScalar>(tm, A, a.base);
-    else bicgstab_system<MIXED, BJ ? kPkBlock : kPkScalar>(tm, A, a.base);
+    else bicgstab_system<MIXED, BJ ? kPkBlock : kPkScalar, LEAN>(tm, A, a.base);
   }
 }
 
