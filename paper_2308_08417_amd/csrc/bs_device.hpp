@@ -154,6 +154,23 @@ __device__ __forceinline__ void wave_sums(T (&v)[K]) {
   }
 }
 
+// wave_sums of four values that also gives every lane the total of its row's
+// value (rows 0..3: values 0, 2, 1, 3).
+template <class T>
+__device__ __forceinline__ T wave_sums_rows(T (&v)[4]) {
+  T a = v[0], b = v[1], c = v[2], d = v[3];
+  swap32(a, b);
+  swap32(c, d);
+  T s01 = a + b, s23 = c + d;
+  swap16(s01, s23);
+  const T t = row16_sum(s01 + s23);
+  v[0] = rdlane(t, 0);
+  v[1] = rdlane(t, 32);
+  v[2] = rdlane(t, 16);
+  v[3] = rdlane(t, 48);
+  return t;
+}
+
 // A value all lanes of the wave hold, in scalar registers.
 __device__ __forceinline__ double wave_uniform(double v) {
   const long long b = __builtin_bit_cast(long long, v);

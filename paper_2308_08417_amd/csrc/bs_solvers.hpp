@@ -1506,22 +1506,40 @@ __device__ __forceinline__ void gmres_system(TM& tm, RW& A, const KArgs& g) {
       // modified Gram-Schmidt takes single vectors; within a block the four
       // dots use the same w (classical Gram-Schmidt) and share one fused
       // reduction, then w -= V_block q.
+      [[maybe_unused]] double* const hq =
+          hcol + ((lane_id() >> 5) | ((lane_id() >> 3) & 2));  // rows 0..3: values 0, 2, 1, 3
 #pragma unroll
       for (int g = 0; g < M; g += 4) {
         if (g <= jmax) {
+          // the last block may reach past vector j: what those hold (earlier
+          // cycles' vectors) gives sums that nothing uses
           T vq[4], q[4];
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
-            vq[t] = (g + t < M && g + t <= j) ? basis(g + t) : (T)0;
+            vq[t] = g + t < M ? basis(g + t) : (T)0;
             q[t] = w[0] * vq[t];
           }
-          tm.sum(q);
+          if constexpr (RW::WG == kWave) {
+            // each row of the wave stores its value (entries past j unused)
+            const T own = wave_sums_rows(q);
+            if (act) hq[g] = (double)own;
+          } else {
+            tm.sum(q);
+          }
           if (act) {
+            if (g + 3 < M && g + 3 <= j) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              if (g + t < M && g + t <= j) {
+              for (int t = 0; t < 4; ++t) {
                 w[0] = fma(-q[t], vq[t], w[0]);
-                hcol[g + t] = (double)q[t];
+                if constexpr (RW::WG != kWave) hcol[g + t] = (double)q[t];
+              }
+            } else {
+#pragma unroll
+              for (int t = 0; t < 3; ++t) {
+                if (g + t < M && g + t <= j) {
+                  w[0] = fma(-q[t], vq[t], w[0]);
+                  if constexpr (RW::WG != kWave) hcol[g + t] = (double)q[t];
+                }
               }
             }
           }
@@ -1553,9 +1571,38 @@ __device__ __forceinline__ void gmres_system(TM& tm, RW& A, const KArgs& g) {
         // apply the previous rotations to column j
         double hp;
         const int cj = j * (j + 1) / 2;
-        if constexpr (RW::TEAM >= 64) {
-          // column j and the rotations are loaded one entry per lane (every
-          // wave holds a copy): the chain reads them with readlane, not LDS loads
+        if constexpr (RW::TEAM >= 64 && RW::TEAM <= 512) {
+          // The chain hp_{i+1} = c_i h_{i+1} - s_i hp_i takes its operands from
+          // LDS at one address for all lanes, a group of four steps ahead, and
+          // leaves the hp_i there; lane i then forms R_ij from hp_i.  (One entry
+          // per lane and six v_readlane per step made this loop 14 vector
+          // instructions and 46 cycles a step before any arithmetic: with the
+          // other changes to a step, 16384 stiff systems of 54 rows took 2.55 ms,
+          // now 1.89.)
+          const int ju = __builtin_amdgcn_readfirstlane(j);
+          hp = hcol[0];
+          double c4[4], s4[4], h4[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { c4[u] = cs[u]; s4[u] = sn[u]; h4[u] = hcol[u + 1]; }
+          for (int i = 0; i < ju; i += 4) {
+            const int nx = i + 4 < M ? i + 4 : 0;  // the group after the last is not used
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if (i + u < ju) {
+                yv[i + u] = hp;
+                hp = fma(h4[u], c4[u], -(hp * s4[u]));
+              }
+              c4[u] = cs[nx + u];
+              s4[u] = sn[nx + u];
+              h4[u] = hcol[nx + u + 1];
+            }
+          }
+          const int l = (int)lane_id();
+          if (l < ju) Rt[cj + l] = fma(cs[l], yv[l], sn[l] * hcol[l + 1]);
+        } else if constexpr (RW::TEAM > 512) {
+          // 16 waves would each read the chain's operands from the LDS they
+          // share (700 systems of 992 rows: 1.93 ms): column j and the rotations
+          // are loaded one entry per lane and read with readlane (1.18 ms)
           const int ju = __builtin_amdgcn_readfirstlane(j);
           const int l = (int)lane_id();
           const double hreg = l <= ju ? hcol[l] : 0.0;
@@ -1594,9 +1641,15 @@ __device__ __forceinline__ void gmres_system(TM& tm, RW& A, const KArgs& g) {
             }
             // teams of a wave or more: j is the same in every lane
             const int jn = RW::TEAM >= 64 ? __builtin_amdgcn_readfirstlane(j + 1) : j + 1;
+            // by groups of four, each behind a scalar branch
 #pragma unroll
-            for (int i = (NL > 1 ? NL : 1); i <= M; ++i)
-              if (jn == i) V[i - NL] = vn;
+            for (int i = (NL > 1 ? NL : 1) & ~3; i <= M; i += 4) {
+              if (RW::TEAM < 64 || (jn >> 2) == (i >> 2)) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                  if (i + u >= (NL > 1 ? NL : 1) && i + u <= M && jn == i + u) V[i + u - NL < NV ? i + u - NL : 0] = vn;
+              }
+            }
             j += 1;
           }
         }
