@@ -826,6 +826,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
   prologue<PK>(tm, A, g, P);
   constexpr int R = RW::R;
   static_assert(!LEAN || (!MIXED && PK == kPkScalar), "lean: FP64, scalar Jacobi or none");
+  constexpr bool kUniform = LEAN || (!MIXED && RW::NZ >= 64 && RW::ROWS > kWave);
   // LEAN: vectors kept in the lane's own LDS cells
   auto keep = [&](int q, const double(&u)[R]) {
     if constexpr (LEAN) {
@@ -839,9 +840,10 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       for (int i = 0; i < R; ++i) u[i] = lds_load<double>(tm.lean_cell(q, i));
     }
   };
-  // LEAN: a lane-uniform value moved to scalar registers
+  // LEAN, and rows of 64 slots on several waves: a team's scalar moved to scalar
+  // registers
   auto uni = [&](auto u) {
-    if constexpr (LEAN) return wave_uniform(u);
+    if constexpr (kUniform) return wave_uniform(u);
     else return u;
   };
 
