@@ -1007,7 +1007,11 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
       lds = without;
     }
   }
-  const int64_t resident = (int64_t)pl.k->occupancy((unsigned)lds + 1024) * cus;
+  // A call of no more groups than compute units has them all resident: it is
+  // not worth the runtime's occupancy query (200 tridiagonal systems of 60 rows,
+  // call to call: 18.5 us with it, 18.2 without).
+  const int64_t resident =
+      groups <= cus ? groups : (int64_t)pl.k->occupancy((unsigned)lds + 1024) * cus;
   const int64_t grid = std::min(groups, resident);
   const hipError_t e = pl.k->launch(a, (unsigned)grid, (unsigned)lds, (hipStream_t)stream);
   return e == hipSuccess ? BS_OK : hip_fail(e, "solver launch");
