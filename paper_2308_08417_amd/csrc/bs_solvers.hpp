@@ -442,6 +442,8 @@ __device__ __forceinline__ void tri_cells(TM& tm, const KArgs& g, unsigned reg, 
     lds_store<double>(reg + L.f + (g.noff + g.n) * 8, 0.0);
     lds_store<double>(reg + L.f + (g.noff + g.n + 1) * 8, 0.0);
     lds_store<double>(reg + L.y + g.n * 8, 0.0);
+    // a record's four values of a one-row system reach one cell further
+    if (g.n == 1) lds_store<double>(reg + L.f + 3 * 8, 0.0);
   }
   tm.lists = true;
 }
@@ -649,6 +651,9 @@ __device__ void ilu_setup_mw(TM& tm, const RW& A, const KArgs& g) {
     }
     tm.sync();
   }
+  // an infinite quotient of this system left no number in the discard cell,
+  // which the records of the smallest systems read (against the zero cell)
+  if (threadIdx.x == 0) lds_store<double>(F + (g.noff + g.n) * 8, 0.0);
   bool bad = false, wide = false;
   if (ok) {
     const double d = lds_load<double>(D + (tm.place >> 16) * 8);

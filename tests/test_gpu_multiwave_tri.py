@@ -100,3 +100,21 @@ def test_row_without_diagonal(r):
         for solver in (bs.TRSV_LOWER, bs.TRSV_UPPER):
             x, _, _, st = solve(bt, fmt, solver)
             assert np.all(st == bs.BREAKDOWN) and np.all(x == 0)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5])
+def test_after_a_zero_pivot(n):
+    """Forced teams of the smallest systems, many per workgroup: a system whose pivots vanish
+    (infinite quotients) leaves nothing behind that the next ones of its workgroup read; they
+    give what they give alone."""
+    bt = W.chem_jacobian(n_batch=9000, n=n, fill=1.0, gamma=1e-4, seed=n)
+    bt.values[::3, 0] = 0.0
+    for solver in ITERATIVE:
+        x, it, _, st = solve(bt, bs.CSR, solver, 128, max_iter=20)
+        keep = np.flatnonzero(np.arange(9000) % 3 != 0)
+        ok = W.Batch(bt.name, n, bt.row_ptr, bt.col_idx, np.ascontiguousarray(bt.values[keep]),
+                     np.ascontiguousarray(bt.b[keep]), np.zeros((keep.size, n)))
+        xo, ito, _, sto = solve(ok, bs.CSR, solver, 128, max_iter=20)
+        assert np.all(sto == bs.CONVERGED)
+        assert np.array_equal(st[keep], sto) and np.array_equal(it[keep], ito)
+        assert np.array_equal(x[keep], xo)
