@@ -341,10 +341,17 @@ __device__ __forceinline__ Eight eight(unsigned at) {
 // Unrolled over all 64 columns, so that lanes and masks are constants (a lane
 // number from a scalar register costs a step 16 more cycles) and the reads of
 // the next eight entries issue in the gaps of a group's chain; groups past n8
-// are skipped.  A group reads ahead up to eight doubles past the row.
-template <bool UP, class STEP>
-__device__ __forceinline__ void sweep_columns(unsigned fi, int n8, STEP step) {
+// are skipped.  A group reads ahead up to eight doubles past the row.  CUT: the
+// columns n .. n8-1 hold other rows' entries, taken as zero (decreasing order,
+// where they are the first group's).
+template <bool UP, bool CUT = false, class STEP>
+__device__ __forceinline__ void sweep_columns(unsigned fi, int n8, STEP step, [[maybe_unused]] int n = 0) {
+  static_assert(!UP || !CUT, "an increasing sweep masks its own columns past the rows");
   Eight t = eight(fi + (UP ? 0 : n8 - 8) * 8);
+  if constexpr (CUT) {
+#pragma unroll
+    for (int q = 1; q < 8; ++q) t.v[q] = n8 - 8 + q < n ? t.v[q] : 0.0;
+  }
 #pragma unroll
   for (int h = 0; h < 8; ++h) {
     const int k0 = UP ? 8 * h : 56 - 8 * h;
@@ -1138,7 +1145,10 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
 // it: x_k = acc_k / t_kk (final on lane k when column k is reached) is read
 // out, and every later row subtracts t_ik x_k.  A sweep reads a lane's row at
 // every column; what lies there outside the triangle belongs to other rows,
-// and the lanes that would meet it take no term.  A zero diagonal entry is a
+// and the lanes that would meet it take no term.  The columns past n, which an
+// upper sweep reaches first with every row, are cut to zero: the x there is
+// zero too, but another row's infinite diagonal (a row whose x is zero, and no
+// error) would make its product no number.  A zero diagonal entry is a
 // breakdown (x = 0); iterations: 0.
 template <bool LOWER, class TM, class RW>
 __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
@@ -1180,11 +1190,14 @@ __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
     const double dv = ok ? 1.0 / tii : 0.0;
     const uint64_t rows = ~0ull >> (kWave - n);  // idle lanes take no term
     double acc = ok ? b[0] : 0.0;
-    sweep_columns<LOWER>(fi, n8, [&](int k, double f) {
-      const double xk = rdlane(acc * dv, k);
-      if (__builtin_amdgcn_inverse_ballot_w64((LOWER ? lanes_past(k) : ~(~0ull << k)) & rows))
-        acc = fma(-f, xk, acc);
-    });
+    sweep_columns<LOWER, !LOWER>(
+        fi, n8,
+        [&](int k, double f) {
+          const double xk = rdlane(acc * dv, k);
+          if (__builtin_amdgcn_inverse_ballot_w64((LOWER ? lanes_past(k) : ~(~0ull << k)) & rows))
+            acc = fma(-f, xk, acc);
+        },
+        n);
     x[0] = ok ? acc * dv : 0.0;
     if (tm.live && wave_any(ok && !finite(x[0]))) stt = ST_NONFINITE;
   }
