@@ -553,7 +553,10 @@ int make_plan(bs_format fmt, int n, int nnz, int max_row, int width, bs_solver s
   // ILU(0) and the triangular solves are bound by their substitution chains,
   // not by loading the values: their LDS goes to more resident waves instead
   // of staging
-  if (waves == 1 && !tri && bs::stage_total_bytes(teams, stored, n, k->nz) <= kStageBudget)
+  // Nor is anything staged where nothing is stored: the copy would read from
+  // an array of no element.
+  if (waves == 1 && !tri && stored > 0 &&
+      bs::stage_total_bytes(teams, stored, n, k->nz) <= kStageBudget)
     stage = 1;
   // Multi-wave teams, CSR, rows of many slots: each system's values copied
   // into LDS by the whole group (coalesced direct-to-LDS loads issued during
@@ -910,10 +913,10 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   a.restart = restart;
   a.stage = pl.info.stage_values;
   a.gmres = solver == BS_GMRES ? 1 : 0;
+  const int stored = fmt == BS_CSR ? pattern->nnz : pattern->width * pattern->n;
   if (!streamed) {
     const int rows = pl.info.team * pl.info.rows_per_lane;
     const int teams = pl.info.systems_per_group, waves = pl.info.group_size / bs::kWave;
-    const int stored = fmt == BS_CSR ? pattern->nnz : pattern->width * pattern->n;
     a.team_bytes = bs::team_vec_bytes(rows, a.gmres, pl.info.group_size,
                                       a.gmres && opts && opts->precision == BS_MIXED);
     // block Jacobi (inverse and exchange buffer) or ILU(0) (factors) after the
@@ -931,7 +934,7 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
     // or the triangle, which the solve no longer needs by then; where the
     // block is longer than the registers kept for it, or than the region, the
     // rows are read straight from memory.
-    if ((ilu || trsv) && solver != BS_GMRES && pl.info.team == bs::kWave &&
+    if (stored > 0 && (ilu || trsv) && solver != BS_GMRES && pl.info.team == bs::kWave &&
         a.stage_vals_bytes <= bs::pf_chunks(pl.info.slots) * 1024 &&
         a.stage_vals_bytes + bs::round16(pattern->n * 8) + 16 <= a.team_bytes - a.bj_offset)
       a.stage = 3;
@@ -962,7 +965,6 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   a.noff = pattern->noff;
   a.ilu64 = pattern->d_base;
   a.ilu64_records = pattern->ilu64_records;
-  a.values = values;
   a.b = b;
   a.x = x;
   a.iters = iters;
@@ -971,6 +973,9 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   a.outer = opts ? opts->outer_iters : nullptr;
   a.sink = bs::device_sink();
   if (!a.sink) return BS_ERR_HIP;
+  // Slots without an entry read a system's first value and drop it; where no
+  // system has one they read the sink instead.
+  a.values = stored > 0 ? values : reinterpret_cast<const double*>(a.sink);
   a.x_alt = opts ? opts->x_alt : nullptr;
   a.alt_used = opts ? opts->alt_used : nullptr;
   if (a.x_alt && (flags & BS_FLAG_X0_ZERO)) return BS_ERR_INVALID_ARG;
