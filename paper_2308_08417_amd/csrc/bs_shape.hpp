@@ -123,7 +123,8 @@ struct Shape {
   // to 256 with the team's scalars in scalar registers, so that two workgroups
   // instead of one fit a compute unit (16384 systems of 144 rows, up to 60
   // entries long: 522 us, now 363).  One-wave ones gain nothing by it (8192
-  // dense systems of 60 rows: 89.2 us and 90.5).
+  // dense systems of 60 rows: 89.2 us and 90.5), and block Jacobi has no room
+  // for it (OCC_BLOCK).
   static constexpr int OCC =
       (WAVES == 1 && R == 1 && NZ >= 24 && NZ <= 32)        ? BS_OCC_ONE_WAVE
       : (R == 1 && (NZ == 56 || (NZ == 64 && WAVES > 1)))   ? 2
@@ -136,6 +137,10 @@ struct Shape {
 #endif
   static constexpr int OCC_MIXED =
       (WAVES == 1 && R == 1 && NZ >= 24 && NZ <= 32) ? BS_OCC_ONE_WAVE_MIXED : 1;
+  // Block Jacobi: its 64-slot forms of several waves take 268 registers and
+  // spill 10 to 13 when held to 256 (967 systems of 250 rows, 62 entries each: BiCGSTAB
+  // 241 us so, 192 at one wave per SIMD; CG 220 and 168).
+  static constexpr int OCC_BLOCK = (R == 1 && NZ == 64 && WAVES > 1) ? 1 : OCC;
 };
 
 // Multi-wave teams copy a system's CSR values into LDS with the whole group

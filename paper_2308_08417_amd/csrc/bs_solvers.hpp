@@ -1854,7 +1854,7 @@ constexpr int kTriOcc = S::TEAM > kWave && S::TEAM < 1024 && S::NZ <= (TRSV ? 32
                             : S::OCC_MIXED;
 
 template <class S, bool MIXED, int PK = kPkScalar>
-__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(PK == kPkIlu ? kTriOcc<S, false> : MIXED ? S::OCC_MIXED : S::OCC))) void k_bicgstab(const KArgs g) {
+__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(PK == kPkIlu ? kTriOcc<S, false> : MIXED ? S::OCC_MIXED : PK == kPkBlock ? S::OCC_BLOCK : S::OCC))) void k_bicgstab(const KArgs g) {
   BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (PK == kPkIlu ? kRegBlock<S> : 0),
                      (bicgstab_system<MIXED, PK>(tm, A, ga)))
 }
@@ -1865,7 +1865,7 @@ __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(kTriOcc<S
 }
 
 template <class S, int PK = kPkScalar>
-__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(S::OCC))) void k_cg(const KArgs g) {
+__global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(PK == kPkBlock ? S::OCC_BLOCK : S::OCC))) void k_cg(const KArgs g) {
   BS_PERSISTENT_LOOP(false, 0, (cg_system<PK>(tm, A, ga)))
 }
 
