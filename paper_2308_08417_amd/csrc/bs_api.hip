@@ -1005,7 +1005,12 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   // the group-wide copy lands in whole KiB behind the vectors: inside the launch's LDS
   if (a.stage == 2 && (a.stage_vals_bytes % 1024 != 0 || a.stage_offset + a.stage_vals_bytes > lds))
     return BS_ERR_UNSUPPORTED;
-  if (a.stage == 2) {  // the group-wide copy of the values only where no group is lost to it
+  // The group-wide copy of the values only where no group is lost to it; rows of
+  // more than 56 slots keep it at that price: lanes
+  // that read such rows from memory touch a line each and load (967 systems of 250
+  // rows, 62 entries each, two groups without the copy and one with it: BiCGSTAB
+  // 207 and 137 us, CG 196 and 121; 2016 of 120 rows, four and two: 179 and 132).
+  if (a.stage == 2 && pl.k->nz <= 56) {
     const int without = lds - a.stage_vals_bytes;
     if (pl.k->occupancy((unsigned)lds + 1024) < pl.k->occupancy((unsigned)without + 1024)) {
       a.stage = 0;
