@@ -1593,21 +1593,29 @@ __device__ __forceinline__ void gmres_system(TM& tm, RW& A, const KArgs& g) {
         const int cj = j * (j + 1) / 2;
         if constexpr (RW::TEAM >= 64 && RW::TEAM <= 512) {
           // The chain hp_{i+1} = c_i h_{i+1} - s_i hp_i takes its operands from
-          // LDS at one address for all lanes, a group of four steps ahead, and
+          // LDS at one address for all lanes, a group of G steps ahead, and
           // leaves the hp_i there; lane i then forms R_ij from hp_i.  (One entry
           // per lane and six v_readlane per step made this loop 14 vector
           // instructions and 46 cycles a step before any arithmetic: with the
-          // other changes to a step, 16384 stiff systems of 54 rows took 2.55 ms,
-          // now 1.89.)
+          // other changes to a step, 16384 stiff systems of 54 rows took 2.40 ms,
+          // now 1.84.)  Groups of four take 48 registers: one-wave shapes afford
+          // them, their LDS holds them to two or three waves per SIMD as it is
+          // (8928 of 60 rows, 28 entries each: 349 us, 378 in groups of two).  Teams
+          // of several waves would lose a resident wave or two to them (3906 systems
+          // of 120 rows, 32 entries each: 640 us, 438 in groups of two, 494 with the
+          // readlane form), and the 4-slot shapes one to groups of two as well
+          // (10000 of 500 rows, 3 each, block Jacobi on 512 lanes: 25 ms, 19 with
+          // single steps, 23 with the readlane form).
           const int ju = __builtin_amdgcn_readfirstlane(j);
+          constexpr int G = RW::WG == kWave ? 4 : RW::NZ <= 4 ? 1 : 2;
           hp = hcol[0];
-          double c4[4], s4[4], h4[4];
+          double c4[G], s4[G], h4[G];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) { c4[u] = cs[u]; s4[u] = sn[u]; h4[u] = hcol[u + 1]; }
-          for (int i = 0; i < ju; i += 4) {
-            const int nx = i + 4 < M ? i + 4 : 0;  // the group after the last is not used
+          for (int u = 0; u < G; ++u) { c4[u] = cs[u]; s4[u] = sn[u]; h4[u] = hcol[u + 1]; }
+          for (int i = 0; i < ju; i += G) {
+            const int nx = i + G < M ? i + G : 0;  // the group after the last is not used
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < G; ++u) {
               if (i + u < ju) {
                 yv[i + u] = hp;
                 hp = fma(h4[u], c4[u], -(hp * s4[u]));

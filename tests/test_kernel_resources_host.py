@@ -74,3 +74,13 @@ def table():
 def test_block_jacobi_of_long_rows(table, team, kernel, args):
     """64 slots on several waves with block Jacobi: nothing in scratch."""
     assert table[(kernel, (team, 1, 64), args)][1] == 0
+
+
+@pytest.mark.parametrize("team", [128, 256, 512])
+@pytest.mark.parametrize("nz,waves", [(4, 4), (8, 3), (16, 3), (32, 2)])
+@pytest.mark.parametrize("args", [(0, 0), (0, 1), (1, 0)])
+def test_gmres_on_several_waves(table, team, nz, waves, args):
+    """FP64, block Jacobi and mixed: the waves per SIMD that rows and basis leave room
+    for, nothing in scratch."""
+    got, scratch = table[("k_gmres", (team, 1, nz), args)]
+    assert got >= waves and scratch == 0
