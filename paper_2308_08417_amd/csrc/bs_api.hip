@@ -935,7 +935,7 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
     // block is longer than the registers kept for it, or than the region, the
     // rows are read straight from memory.
     if (stored > 0 && (ilu || trsv) && solver != BS_GMRES && pl.info.team == bs::kWave &&
-        a.stage_vals_bytes <= bs::pf_chunks(pl.info.slots) * 1024 &&
+        a.stage_vals_bytes <= bs::pf_chunks(pl.info.slots, trsv) * 1024 &&
         a.stage_vals_bytes + bs::round16(pattern->n * 8) + 16 <= a.team_bytes - a.bj_offset)
       a.stage = 3;
     // CSR rows go through a fixed window when the block holds a full window

@@ -98,8 +98,13 @@ __host__ __device__ constexpr int trsv_bytes(int n) { return ((n * (n + 1) / 2 +
 
 // ILU(0) and BatchTrsv on one-wave teams: KiB of a system's values a wave keeps
 // in registers while it solves the system before (16 bytes per lane and KiB).
-// Shapes beyond 32 slots have no registers left for them.
-__host__ __device__ constexpr int pf_chunks(int nz) { return nz <= 28 ? 12 : nz <= 32 ? 10 : 0; }
+// Shapes beyond 32 slots have no registers left for them.  BatchTrsv keeps no
+// more than 64 rows of nz slots can hold: its small systems live on resident
+// waves, which twelve KiB cost the shapes of up to 16 slots (16384 lower
+// triangles of 12 rows, 7 entries each: 21 us with twelve, 18 with five).
+__host__ __device__ constexpr int pf_chunks(int nz, bool trsv) {
+  return nz > 32 ? 0 : nz > 28 ? 10 : trsv && nz / 2 + 1 < 12 ? nz / 2 + 1 : 12;
+}
 
 // Flag bit of the absolute stop criterion (BS_FLAG_ABS_TOL).
 constexpr int kFlagAbsTol = 4;

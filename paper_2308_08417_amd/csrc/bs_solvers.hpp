@@ -325,45 +325,49 @@ __device__ void ilu_setup(TM& tm, RW& A, const KArgs& g, double (&d)[RW::R]) {
   wave_lds_fence();
 }
 
-// Eight consecutive doubles of a lane's row.
-struct Eight {
-  double v[8];
+// G consecutive doubles of a lane's row.  ILU(0) takes groups of eight (its rows
+// are padded to that), BatchTrsv of four, which still cover a read's latency and
+// hold 16 registers less.
+template <int G>
+struct Group {
+  double v[G];
 };
-__device__ __forceinline__ Eight eight(unsigned at) {
-  Eight e;
+template <int G>
+__device__ __forceinline__ Group<G> group_at(unsigned at) {
+  Group<G> e;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) e.v[q] = lds_load<double>(at + q * 8);
+  for (int q = 0; q < G; ++q) e.v[q] = lds_load<double>(at + q * 8);
   return e;
 }
 
-// A column sweep over columns 0..n8-1 (n8 a multiple of 8, at most 64) of a
+// A column sweep over columns 0..cols-1 (a multiple of G, at most 64) of a
 // lane's row at fi, in increasing (UP) or decreasing order: step(k, entry).
 // Unrolled over all 64 columns, so that lanes and masks are constants (a lane
 // number from a scalar register costs a step 16 more cycles) and the reads of
-// the next eight entries issue in the gaps of a group's chain; groups past n8
-// are skipped.  A group reads ahead up to eight doubles past the row.  CUT: the
-// columns n .. n8-1 hold other rows' entries, taken as zero (decreasing order,
+// the next G entries issue in the gaps of a group's chain; groups past cols
+// are skipped.  A group reads ahead up to G doubles past the row.  CUT: the
+// columns n .. cols-1 hold other rows' entries, taken as zero (decreasing order,
 // where they are the first group's).
-template <bool UP, bool CUT = false, class STEP>
-__device__ __forceinline__ void sweep_columns(unsigned fi, int n8, STEP step, [[maybe_unused]] int n = 0) {
+template <bool UP, int G, bool CUT = false, class STEP>
+__device__ __forceinline__ void sweep_columns(unsigned fi, int cols, STEP step, [[maybe_unused]] int n = 0) {
   static_assert(!UP || !CUT, "an increasing sweep masks its own columns past the rows");
-  Eight t = eight(fi + (UP ? 0 : n8 - 8) * 8);
+  Group<G> t = group_at<G>(fi + (UP ? 0 : cols - G) * 8);
   if constexpr (CUT) {
 #pragma unroll
-    for (int q = 1; q < 8; ++q) t.v[q] = n8 - 8 + q < n ? t.v[q] : 0.0;
+    for (int q = 1; q < G; ++q) t.v[q] = cols - G + q < n ? t.v[q] : 0.0;
   }
 #pragma unroll
-  for (int h = 0; h < 8; ++h) {
-    const int k0 = UP ? 8 * h : 56 - 8 * h;
-    if (k0 < n8) {
+  for (int h = 0; h < kWave / G; ++h) {
+    const int k0 = UP ? G * h : kWave - G - G * h;
+    if (k0 < cols) {
       // this group's entries first (read a group ago): issued behind the next
       // group's reads, their wait would cover those too
 #pragma unroll
-      for (int q = 0; q < 8; ++q) __asm__ volatile("" : "+v"(t.v[q]));
-      Eight next = t;
-      if (h < 7) next = eight(fi + (UP ? k0 + 8 : k0 - 8) * 8);
+      for (int q = 0; q < G; ++q) __asm__ volatile("" : "+v"(t.v[q]));
+      Group<G> next = t;
+      if (h < kWave / G - 1) next = group_at<G>(fi + (UP ? k0 + G : k0 - G) * 8);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) step(k0 + (UP ? q : 7 - q), t.v[UP ? q : 7 - q]);
+      for (int q = 0; q < G; ++q) step(k0 + (UP ? q : G - 1 - q), t.v[UP ? q : G - 1 - q]);
       t = next;
     }
   }
@@ -405,12 +409,12 @@ __device__ __forceinline__ void ilu_apply(TM& tm, const RW& A, const KArgs& g,
   const uint64_t rows = ~0ull >> (kWave - n);  // idle lanes take no term
   const double dv = (double)d[0], r = 1.0 / dv, e = fma(-dv, r, 1.0) * r;
   double acc = ok ? (double)v[0] : 0.0;
-  sweep_columns<true>(fi, n8, [&](int k, double f) {
+  sweep_columns<true, 8>(fi, n8, [&](int k, double f) {
     const double y = rdlane(acc, k);
     if (__builtin_amdgcn_inverse_ballot_w64(lanes_past(k) & rows)) acc = fma(-f, y, acc);
   });
   const double y0 = acc;
-  sweep_columns<false>(fi, n8, [&](int j, double f) {
+  sweep_columns<false, 8>(fi, n8, [&](int j, double f) {
     const double zj = rdlane(quotient(acc, r, e), j);
     if (__builtin_amdgcn_inverse_ballot_w64(~(~0ull << j) & rows)) acc = fma(-f, zj, acc);
   });
@@ -1153,7 +1157,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
 template <bool LOWER, class TM, class RW>
 __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
   static_assert(RW::R == 1 && RW::TEAM == kWave, "one-wave BatchTrsv");
-  const int n = g.n, n8 = ilu_stride(n) - 1;
+  const int n = g.n;
   const unsigned F = lds_addr(tm.bj_region(g));
   const int lane = tm.lane;
   const bool ok = A.ok[0];
@@ -1190,8 +1194,8 @@ __device__ __forceinline__ void trsv_system_w64(TM& tm, RW& A, const KArgs& g) {
     const double dv = ok ? 1.0 / tii : 0.0;
     const uint64_t rows = ~0ull >> (kWave - n);  // idle lanes take no term
     double acc = ok ? b[0] : 0.0;
-    sweep_columns<LOWER, !LOWER>(
-        fi, n8,
+    sweep_columns<LOWER, 4, !LOWER>(
+        fi, (n + 3) & ~3,
         [&](int k, double f) {
           const double xk = rdlane(acc * dv, k);
           if (__builtin_amdgcn_inverse_ballot_w64((LOWER ? lanes_past(k) : ~(~0ull << k)) & rows))
@@ -1844,8 +1848,8 @@ constexpr bool kLds32 = MIXED && (S::ROWS > kWave);
 // with this and the packed one).  Their LDS goes to more resident waves instead of
 // a staging area, and a lane that reads its own row from memory touches a
 // line of its own with every load.
-template <class S>
-constexpr int kRegBlock = S::TEAM == kWave && S::R == 1 ? pf_chunks(S::NZ) : 0;
+template <class S, bool TRSV>
+constexpr int kRegBlock = S::TEAM == kWave && S::R == 1 ? pf_chunks(S::NZ, TRSV) : 0;
 
 // ILU(0) on one-wave teams: the dense factors (about 25 KB of LDS per wave
 // for 54 rows) leave room for fewer than two waves per SIMD, so the register
@@ -1856,20 +1860,25 @@ constexpr int kRegBlock = S::TEAM == kWave && S::R == 1 ? pf_chunks(S::NZ) : 0;
 // of the row's own across the sweep instead (1024 triangular solves of 256
 // rows: 34.4 us without the limit, 24.6 with it; 700 systems of 182 rows with
 // ILU(0): 325 and 191 us).
+// One-wave BatchTrsv of 4 slots: the packed triangle of a small system leaves
+// room for many waves, whose loads hide one another; six per SIMD at 80
+// registers (16384 lower triangles of 12 rows, 3 entries each: 17.3 us at five,
+// 16.2 at six; 19 at three and with groups of eight columns).
 template <class S, bool TRSV>
 constexpr int kTriOcc = S::TEAM > kWave && S::TEAM < 1024 && S::NZ <= (TRSV ? 32 : 16)
                             ? (S::NZ <= (TRSV ? 16 : 8) ? 4 : 3)
-                            : S::OCC_MIXED;
+                        : TRSV && S::TEAM == kWave && S::NZ == 4 ? 6
+                                                                 : S::OCC_MIXED;
 
 template <class S, bool MIXED, int PK = kPkScalar>
 __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(PK == kPkIlu ? kTriOcc<S, false> : MIXED ? S::OCC_MIXED : PK == kPkBlock ? S::OCC_BLOCK : S::OCC))) void k_bicgstab(const KArgs g) {
-  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (PK == kPkIlu ? kRegBlock<S> : 0),
+  BS_PERSISTENT_LOOP((kLds32<S, MIXED>), (PK == kPkIlu ? kRegBlock<S, false> : 0),
                      (bicgstab_system<MIXED, PK>(tm, A, ga)))
 }
 
 template <class S, bool LOWER>
 __global__ __launch_bounds__(S::WG) __attribute__((amdgpu_waves_per_eu(kTriOcc<S, true>))) void k_trsv(const KArgs g) {
-  BS_PERSISTENT_LOOP(false, kRegBlock<S>, (trsv_system<LOWER>(tm, A, ga)))
+  BS_PERSISTENT_LOOP(false, (kRegBlock<S, true>), (trsv_system<LOWER>(tm, A, ga)))
 }
 
 template <class S, int PK = kPkScalar>

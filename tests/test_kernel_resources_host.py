@@ -84,3 +84,10 @@ def test_gmres_on_several_waves(table, team, nz, waves, args):
     for, nothing in scratch."""
     got, scratch = table[("k_gmres", (team, 1, nz), args)]
     assert got >= waves and scratch == 0
+
+
+@pytest.mark.parametrize("lower", [0, 1])
+@pytest.mark.parametrize("nz,waves", [(4, 6), (8, 4), (16, 3)])
+def test_short_rows_of_one_wave_trsv(table, lower, nz, waves):
+    """Small triangles live on resident waves."""
+    assert table[("k_trsv", (64, 1, nz), (lower,))][0] >= waves
