@@ -615,20 +615,26 @@ __global__ void k_varlen_reset(int* counter);
 // lean, it keeps x, b, the Jacobi diagonal and r^ in the lane's own LDS cells,
 // the team's scalars in scalar registers, and forms M p and M s a second time
 // for the update of x.  8200 systems of 512 to 1024 rows: 2140 us with one
-// workgroup per compute unit, 1456 with two.  From 12 slots on the rows alone
-// leave no room.
-template <class RowsT, int SOLVER, bool MIXED, bool BJ>
-constexpr bool kVarLean = RowsT::SHORT && SOLVER == 1 && !MIXED && !BJ;
-template <class RowsT, int SOLVER, bool MIXED, bool BJ>
-constexpr int kVarOcc = RowsT::SHORT && !MIXED && !BJ ? 4 : RowsT::OCC;
+// workgroup per compute unit, 1456 with two.  The 10-slot form still spills 19
+// to 25 registers and gains by it all the same (4000 systems of 520 to 1000 rows,
+// 9 entries each: 976 us without the second workgroup and the lone teams' barrier,
+// now 548).  From 12 slots on the rows alone leave no room.
+// FEW: a launch of no more tasks than compute units has no second workgroup for
+// any of them, and from the lean form only its longer latency: it takes the form
+// with everything in registers (300 systems of 65 to 128 rows, 9 entries each,
+// 38 tasks: 42.7 us lean, 36.1 so; 60 of 520 to 1000 rows: 62.2 and 54.2).
+template <class RowsT, int SOLVER, bool MIXED, bool BJ, bool FEW = false>
+constexpr bool kVarLean = RowsT::SHORT && SOLVER == 1 && !MIXED && !BJ && !FEW;
+template <class RowsT, int SOLVER, bool MIXED, bool BJ, bool FEW = false>
+constexpr int kVarOcc = RowsT::SHORT && !MIXED && !BJ && !FEW ? 4 : RowsT::OCC;
 
 // RowsT: VarRows<VS, NZ, SRC> (rows in registers) or VarRowsS<VS, SRC>.
-template <class VS, class RowsT, int SOLVER, bool MIXED, bool BJ = false>
-__global__ __launch_bounds__(VS::WG) __attribute__((amdgpu_waves_per_eu((kVarOcc<RowsT, SOLVER, MIXED, BJ>))))
+template <class VS, class RowsT, int SOLVER, bool MIXED, bool BJ = false, bool FEW = false>
+__global__ __launch_bounds__(VS::WG) __attribute__((amdgpu_waves_per_eu((kVarOcc<RowsT, SOLVER, MIXED, BJ, FEW>))))
 void k_varlen(const VArgs va) {
   static_assert(!(MIXED && BJ), "the mixed kernels' per-team blocks carry no block Jacobi");
   // buffers and reduction slots, then (BJ) the block-Jacobi region of the largest block
-  constexpr bool LEAN = kVarLean<RowsT, SOLVER, MIXED, BJ>;
+  constexpr bool LEAN = kVarLean<RowsT, SOLVER, MIXED, BJ, FEW>;
   __shared__ __align__(16) char smem[var_lds_bytes<VS>() + (BJ ? bj_bytes(VS::ROWS, kMaxBlock) : 0) +
                                      (LEAN ? kLeanVectors * VS::ROWS * 8 : 0)];
   __shared__ int task_sh;
@@ -638,7 +644,7 @@ void k_varlen(const VArgs va) {
     const int b = threadIdx.x / VS::MAXT, t = threadIdx.x % VS::MAXT;
     lds_store<double>(lds_base + b * kBuf + (VS::ROWS + t) * 8, 0.0);
   }
-  typename std::conditional<RowsT::SHORT && !MIXED && !BJ, ShortTeam<VS>, VarTeam<VS>>::type tm;
+  typename std::conditional<RowsT::SHORT && !MIXED && !BJ && !FEW, ShortTeam<VS>, VarTeam<VS>>::type tm;
   tm.phase = 0;
   tm.turn = 0;
   for (;;) {

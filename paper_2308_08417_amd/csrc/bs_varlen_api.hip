@@ -420,7 +420,7 @@ int launch(const VarDesc& v, bs::VArgs a, const Plan& pl, const TaskSet& ts, int
     a.counter = counter + l.counter;
     const int64_t resident = (int64_t)cus * std::max(per_cu, 1);
     const unsigned grid = (unsigned)std::min<int64_t>(resident, a.n_tasks);
-    e = l.k->fn(a, grid, stream);
+    e = l.k->fn(a, grid, a.n_tasks <= cus, stream);
     if (e != hipSuccess) return hip_err(e, "uneven-batch launch");
   }
   return BS_OK;

@@ -11,11 +11,18 @@
 
 namespace bs {
 
-typedef hipError_t (*VLaunch)(const VArgs&, unsigned grid, hipStream_t);
+// few: no more tasks than compute units (see kVarLean)
+typedef hipError_t (*VLaunch)(const VArgs&, unsigned grid, bool few, hipStream_t);
 typedef hipError_t (*VOccupancy)(int*);
 
 template <class VS, class RowsT, int SOLVER, bool MIXED, bool BJ>
-hipError_t vlaunch(const VArgs& a, unsigned grid, hipStream_t s) {
+hipError_t vlaunch(const VArgs& a, unsigned grid, bool few, hipStream_t s) {
+  if constexpr (kVarLean<RowsT, SOLVER, MIXED, BJ>) {
+    if (few) {
+      hipLaunchKernelGGL((k_varlen<VS, RowsT, SOLVER, MIXED, BJ, true>), dim3(grid), dim3(VS::WG), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((k_varlen<VS, RowsT, SOLVER, MIXED, BJ>), dim3(grid), dim3(VS::WG), 0, s, a);
   return hipGetLastError();
 }

@@ -49,8 +49,8 @@ def kernels(elf):
 
 
 @pytest.fixture(scope="module")
-def table():
-    """(kernel, template arguments) -> (waves per SIMD, scratch bytes per lane)."""
+def records():
+    """Mangled name -> (waves per SIMD, scratch bytes per lane) of every kernel."""
     if not os.path.exists(build.LIB):
         pytest.skip("the library is not built")
     out = {}
@@ -58,14 +58,21 @@ def table():
         data = f.read()
     for elf in code_objects(data):
         for k in kernels(elf):
-            m = re.match(r"_ZN2bs(?:\d+)(k_[a-z]+)INS_5ShapeILi(\d+)ELi(\d+)ELi(\d+)EEE((?:L[bi]\d+E)*)E",
-                         k[".name"])
-            if m:
-                args = tuple(int(a) for a in re.findall(r"L[bi](\d+)E", m[5]))
-                regs = (k[".vgpr_count"] + 7) // 8 * 8
-                out[(m[1], tuple(int(v) for v in m.group(2, 3, 4)), args)] = (
-                    min(8, 512 // regs), k[".private_segment_fixed_size"])
+            regs = (k[".vgpr_count"] + 7) // 8 * 8
+            out[k[".name"]] = (min(8, 512 // regs), k[".private_segment_fixed_size"])
     assert out
+    return out
+
+
+@pytest.fixture(scope="module")
+def table(records):
+    """(kernel, team shape, other template arguments) -> record, for the fixed-size kernels."""
+    out = {}
+    for name, r in records.items():
+        m = re.match(r"_ZN2bs(?:\d+)(k_[a-z]+)INS_5ShapeILi(\d+)ELi(\d+)ELi(\d+)EEE((?:L[bi]\d+E)*)E", name)
+        if m:
+            args = tuple(int(a) for a in re.findall(r"L[bi](\d+)E", m[5]))
+            out[(m[1], tuple(int(v) for v in m.group(2, 3, 4)), args)] = r
     return out
 
 
@@ -91,3 +98,12 @@ def test_gmres_on_several_waves(table, team, nz, waves, args):
 def test_short_rows_of_one_wave_trsv(table, lower, nz, waves):
     """Small triangles live on resident waves."""
     assert table[("k_trsv", (64, 1, nz), (lower,))][0] >= waves
+
+
+@pytest.mark.parametrize("nz", [8, 10])
+@pytest.mark.parametrize("source", [0, 1, 2])
+def test_uneven_few_tasks(records, nz, source):
+    """BiCGSTAB on 512 lanes x 2 rows for launches of few tasks: everything in registers."""
+    name = (f"_ZN2bs8k_varlenINS_8VarShapeILi512ELi2EEENS_7VarRowsIS2_Li{nz}ELi{source}ELb0EEE"
+            "Li1ELb0ELb0ELb1EEEvNS_5VArgsE")
+    assert records[name][1] == 0
