@@ -128,25 +128,59 @@ constexpr int kTriRows = 1024;
 // Level scheduling of a pattern's triangles (see bs_pattern_s): a row's lower
 // level is one more than the largest lower level among the columns j < i it
 // holds (0 if none), its upper level likewise over the columns j > i, taken
-// from the last row up.
+// from the last row up.  Every pattern that a multi-wave shape can take pays
+// for this when it is created, whatever it is used for, so it works on flat
+// arrays of known size (1000 rows of
+// 9 entries, the whole creation: 431 us with a list per row and growing vectors, now
+// 213).
 void tri_schedule(bs_pattern_s& p) {
   const int n = p.n;
-  std::vector<int> level[2] = {std::vector<int>(n, 0), std::vector<int>(n, 0)};
-  for (int i = 0; i < n; ++i)
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-      if (p.col[e] < i) level[0][i] = std::max(level[0][i], level[0][p.col[e]] + 1);
-  for (int i = n - 1; i >= 0; --i)
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-      if (p.col[e] > i) level[1][i] = std::max(level[1][i], level[1][p.col[e]] + 1);
-  // rows by level, and each row's place among them
-  std::vector<int> order[2], at[2];
+  // the strictly lower (0) and upper (1) entries of each row in increasing
+  // column: row i's are terms[base[t][i] .. +count[t][i]], and that index is
+  // the entry's place in the factor array
+  std::vector<int> terms(p.nnz), base[2], count[2], level[2], order[2], at[2];
   for (int t = 0; t < 2; ++t) {
+    base[t].resize(n);
+    count[t].resize(n);
+    level[t].assign(n, 0);
     order[t].resize(n);
     at[t].resize(n);
-    for (int i = 0; i < n; ++i) order[t][i] = i;
-    std::stable_sort(order[t].begin(), order[t].end(),
-                     [&](int x, int y) { return level[t][x] < level[t][y]; });
-    for (int q = 0; q < n; ++q) at[t][order[t][q]] = q;
+  }
+  p.pos.assign(p.nnz, 0);
+  p.noff = 0;
+  std::vector<std::pair<int, int>> row;
+  for (int i = 0; i < n; ++i) {
+    const int e0 = p.row_ptr[i], e1 = p.row_ptr[i + 1];
+    bool sorted = true;
+    for (int e = e0 + 1; e < e1; ++e) sorted = sorted && p.col[e - 1] < p.col[e];
+    row.clear();
+    if (!sorted) {
+      for (int e = e0; e < e1; ++e) row.push_back({p.col[e], e});
+      std::sort(row.begin(), row.end());
+    }
+    base[0][i] = p.noff;
+    count[0][i] = count[1][i] = 0;
+    for (int q = e0; q < e1; ++q) {
+      const int j = sorted ? p.col[q] : row[q - e0].first, e = sorted ? q : row[q - e0].second;
+      if (j == i) continue;
+      ++count[j > i][i];
+      p.pos[e] = (unsigned short)p.noff;
+      terms[p.noff++] = j;
+    }
+    base[1][i] = base[0][i] + count[0][i];
+  }
+  auto of = [&](int t, int i) { return terms.data() + base[t][i]; };
+  for (int i = 0; i < n; ++i)
+    for (int q = 0; q < count[0][i]; ++q) level[0][i] = std::max(level[0][i], level[0][of(0, i)[q]] + 1);
+  for (int i = n - 1; i >= 0; --i)
+    for (int q = 0; q < count[1][i]; ++q) level[1][i] = std::max(level[1][i], level[1][of(1, i)[q]] + 1);
+  // rows by level, in increasing order inside one, and each row's place among them
+  std::vector<int> first;
+  for (int t = 0; t < 2; ++t) {
+    first.assign(n + 1, 0);
+    for (int i = 0; i < n; ++i) ++first[level[t][i] + 1];
+    for (int l = 0; l < n; ++l) first[l + 1] += first[l];
+    for (int i = 0; i < n; ++i) order[t][at[t][i] = first[level[t][i]]++] = i;
   }
   p.place.resize(n);
   p.lev.resize(n);
@@ -157,104 +191,91 @@ void tri_schedule(bs_pattern_s& p) {
     p.up[q] = at[1][order[0][q]];
   }
   p.nlev = p.lev.back() + 1;
-  // each row's terms by increasing column, and their places
-  std::vector<std::vector<int>> terms[2];  // columns
-  std::vector<int> base[2];
-  p.pos.assign(p.nnz, 0);
-  p.noff = 0;
-  for (int t = 0; t < 2; ++t) {
-    terms[t].resize(n);
-    base[t].resize(n);
-  }
-  std::vector<std::pair<int, int>> row;
-  for (int i = 0; i < n; ++i) {
-    row.clear();
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) row.push_back({p.col[e], e});
-    std::sort(row.begin(), row.end());
-    for (int t = 0; t < 2; ++t) {
-      base[t][i] = p.noff;
-      for (const auto& c : row)
-        if (t == 0 ? c.first < i : c.first > i) {
-          p.pos[c.second] = (unsigned short)p.noff++;
-          terms[t][i].push_back(c.first);
-        }
-    }
-  }
   const int diag0 = p.noff;
   for (int i = 0; i < n; ++i)
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e)
-      if (p.col[e] == i) p.pos[e] = (unsigned short)(diag0 + at[1][i]);
+    if (p.diag_slot[i] >= 0) p.pos[p.row_ptr[i] + p.diag_slot[i]] = (unsigned short)(diag0 + at[1][i]);
   // sweep segments
+  struct Step { int first, rows, most; };  // place of the first row, rows, their longest row
+  std::vector<Step> steps;
   for (int t = 0; t < 2; ++t) {
-    std::vector<std::pair<int, int>> steps;  // first place, rows
-    for (int q = 0; q < n;) {
-      int c = 1;
-      while (c < bs::kWave && q + c < n && level[t][order[t][q + c]] == level[t][order[t][q]]) ++c;
-      steps.push_back({q, c});
-      q += c;
-    }
-    int w = 0;
-    for (const auto& st : steps)
-      while ((1 << w) < st.second) ++w;
-    p.wseg[t] = w;
-    p.seg[t].clear();
-    p.nseg[t] = 0;
+    steps.clear();
+    int w = 0, total = 0;
     p.one_seg[t] = true;
-    for (const auto& st : steps) {
-      size_t most = 1;
-      for (int l = 0; l < st.second; ++l) most = std::max(most, terms[t][order[t][st.first + l]].size());
-      p.one_seg[t] = p.one_seg[t] && most <= 4;
-      for (size_t k0 = 0; k0 < most; k0 += 4) {
-        for (int l = 0; l < (1 << w); ++l) {
-          const int i = l < st.second ? order[t][st.first + l] : -1;
-          unsigned col[4], r[4] = {0, 0, (unsigned)(n + 1) * 8 * 0x10001u, 0};
-          for (unsigned& c : col) c = (unsigned)n * 8;
-          if (i >= 0) {
-            const std::vector<int>& tm = terms[t][i];
-            int c = 0;
-            for (; c < 4 && k0 + c < tm.size(); ++c) col[c] = (unsigned)at[t][tm[k0 + c]] * 8;
-            r[2] = (unsigned)at[t][i] * 8 | ((unsigned)at[1][i] * 8 << 16);
-            r[3] = (unsigned)(c ? base[t][i] + (int)k0 : 0) | ((unsigned)c << 16) |
-                   (k0 == 0 ? 1u << 30 : 0u) | (k0 + 4 >= most ? 1u << 31 : 0u);
-          }
-          r[0] = col[0] | (col[1] << 16);
-          r[1] = col[2] | (col[3] << 16);
-          for (unsigned v : r) p.seg[t].push_back((int)v);
-        }
-        ++p.nseg[t];
-      }
+    for (int q = 0; q < n;) {
+      Step st{q, 0, 1};
+      const int l = level[t][order[t][q]];
+      for (; st.rows < bs::kWave && q < n && level[t][order[t][q]] == l; ++q, ++st.rows)
+        st.most = std::max(st.most, count[t][order[t][q]]);
+      while ((1 << w) < st.rows) ++w;
+      total += (st.most + 3) / 4;
+      p.one_seg[t] = p.one_seg[t] && st.most <= 4;
+      steps.push_back(st);
     }
-    const int total = (p.nseg[t] + 3) / 4 * 4;
-    for (int k = p.nseg[t]; k < total + 4; ++k)
-      for (int l = 0; l < (1 << w); ++l)
-        for (unsigned v : {(unsigned)n * 8 * 0x10001u, (unsigned)n * 8 * 0x10001u,
-                           (unsigned)(n + 1) * 8 * 0x10001u, 0u})
-          p.seg[t].push_back((int)v);
-    p.nseg[t] = total;
+    p.wseg[t] = w;
+    p.nseg[t] = (total + 3) / 4 * 4;
+    // records without a row, then the rows' over them
+    const unsigned zero = (unsigned)n * 8 * 0x10001u, spare = (unsigned)(n + 1) * 8 * 0x10001u;
+    p.seg[t].resize(((size_t)(p.nseg[t] + 4) << w) * 4);
+    unsigned* r = reinterpret_cast<unsigned*>(p.seg[t].data());
+    for (size_t k = 0; k < p.seg[t].size(); k += 4) {
+      r[k] = r[k + 1] = zero;
+      r[k + 2] = spare;
+      r[k + 3] = 0;
+    }
+    for (const Step& st : steps) {
+      for (int l = 0; l < st.rows; ++l) {
+        const int i = order[t][st.first + l],* tm = of(t, i), own = at[t][i] * 8 | (at[1][i] * 8 << 16);
+        unsigned* s = r + (size_t)l * 4;
+        for (int k0 = 0; k0 < st.most; k0 += 4, s += (size_t)4 << w) {
+          unsigned col[4];
+          int c = 0;
+          for (; c < 4 && k0 + c < count[t][i]; ++c) col[c] = (unsigned)at[t][tm[k0 + c]] * 8;
+          for (int q = c; q < 4; ++q) col[q] = (unsigned)n * 8;
+          s[0] = col[0] | (col[1] << 16);
+          s[1] = col[2] | (col[3] << 16);
+          s[2] = (unsigned)own;
+          s[3] = (unsigned)(c ? base[t][i] + k0 : 0) | ((unsigned)c << 16) | (k0 == 0 ? 1u << 30 : 0u) |
+                 (k0 + 4 >= st.most ? 1u << 31 : 0u);
+        }
+      }
+      r += ((size_t)((st.most + 3) / 4) << w) * 4;
+    }
   }
-  // The ILU(0) schedule (symbolic factorization, the IKJ form).
+  // The ILU(0) schedule (symbolic factorization, the IKJ form): for a lower
+  // entry (i,k) at most a group per four upper entries of row k, and at least one.
+  size_t most = 0;
+  for (int i = 0; i < n; ++i)
+    for (int q = 0; q < count[0][i]; ++q) most += (size_t)std::max((count[1][of(0, i)[q]] + 3) / 4, 1);
   const unsigned discard = (unsigned)(diag0 + n), zero = discard + 1;
   p.ilu_ptr.assign(n + 1, 0);
-  p.ilu_ops.clear();
-  std::vector<int> where(n, -1);
+  p.ilu_ops.resize(most * 5);
+  unsigned* ops = reinterpret_cast<unsigned*>(p.ilu_ops.data());
+  unsigned* out = ops;
+  std::vector<int> where(n, -1);  // place of (i, j), for the row i at hand
   for (int q0 = 0; q0 < n; ++q0) {
     const int i = order[0][q0];
-    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = e;
-    for (int k : terms[0][i]) {
-      std::vector<unsigned> up;
-      for (int e = p.row_ptr[k]; e < p.row_ptr[k + 1]; ++e) {
-        const int j = p.col[e];
-        if (j > k && where[j] >= 0) up.push_back((unsigned)p.pos[e] << 16 | p.pos[where[j]]);
+    for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = p.pos[e];
+    for (int q = 0; q < count[0][i]; ++q) {
+      const int k = of(0, i)[q], * uk = of(1, k);
+      unsigned head = 1u << 31 | (unsigned)(diag0 + at[1][k]) << 15 | (unsigned)(base[0][i] + q);
+      int u = 0;
+      for (int c = 0; c < count[1][k]; ++c) {
+        const int w = where[uk[c]];
+        if (w < 0) continue;
+        if ((u & 3) == 0) {
+          *out++ = head;
+          head = 0;
+        }
+        *out++ = (unsigned)(base[1][k] + c) << 16 | (unsigned)w;
+        ++u;
       }
-      for (size_t at0 = 0; at0 == 0 || at0 < up.size(); at0 += 4) {
-        p.ilu_ops.push_back(at0 ? 0 : (int)(1u << 31 | (unsigned)(diag0 + at[1][k]) << 15 | p.pos[where[k]]));
-        for (size_t q = at0; q < at0 + 4; ++q)
-          p.ilu_ops.push_back((int)(q < up.size() ? up[q] : zero << 16 | discard));
-      }
+      if (u == 0) *out++ = head;
+      for (; u == 0 || (u & 3); ++u) *out++ = zero << 16 | discard;
     }
     for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) where[p.col[e]] = -1;
-    p.ilu_ptr[q0 + 1] = (int)p.ilu_ops.size();
+    p.ilu_ptr[q0 + 1] = (int)(out - ops);
   }
+  p.ilu_ops.resize(out - ops);
 }
 
 const bs::KernelEntry* find_kernel(int variant, int team, int r, int nz_min);
@@ -294,36 +315,43 @@ void derive(bs_pattern_s& p) {
   // The one-wave schedule: rows and columns as 64-bit masks.
   p.ilu64.clear();
   if (n <= bs::kWave) {
-    std::vector<uint64_t> row(n, 0), col(n, 0);
+    uint64_t row[bs::kWave] = {0}, col[bs::kWave] = {0};
     for (int i = 0; i < n; ++i)
       for (int e = p.row_ptr[i]; e < p.row_ptr[i + 1]; ++e) {
         row[i] |= 1ull << p.col[e];
         col[p.col[e]] |= 1ull << i;
       }
     const int stride = bs::ilu_stride(n) * 8;
+    // a pivot has at most a record for every four of its columns, and one
+    p.ilu64.resize(((size_t)n * (bs::kWave / 4 + 1) + 4) * 16);
+    unsigned* w = reinterpret_cast<unsigned*>(p.ilu64.data());
     for (int k = 0; k + 1 < n; ++k) {
       const uint64_t later = (~0ull << k) << 1, below = col[k] & later;
       if (!below) continue;
-      std::vector<int> js;
-      for (int j = k + 1; j < n; ++j)
-        if ((row[k] >> j & 1) && (col[j] & below)) js.push_back(j);
-      for (size_t at = 0; at == 0 || at < js.size(); at += 4) {
-        unsigned w[16] = {0};
+      uint64_t js = row[k] & later;  // columns of row k ..
+      for (uint64_t m = js; m; m &= m - 1)  // .. that a row below holds
+        if (!(col[__builtin_ctzll(m)] & below)) js &= ~(m & -m);
+      bool head = true;
+      do {
         for (int q = 0; q < 4; ++q) {
-          const bool has = at + q < js.size();
-          const uint64_t rows = has ? col[js[at + q]] & below : 0;
+          const int j = js ? __builtin_ctzll(js) : k;
+          const uint64_t rows = js ? col[j] & below : 0;
+          js &= js - 1;
           w[2 * q] = (unsigned)rows;
           w[2 * q + 1] = (unsigned)(rows >> 32);
-          w[8 + q] = (unsigned)(has ? js[at + q] : k) * 8;
+          w[8 + q] = (unsigned)j * 8;
         }
         w[12] = (unsigned)below;
         w[13] = (unsigned)(below >> 32);
-        w[14] = (unsigned)(k * 8) | (at == 0 ? 1u << 31 : 0u);
+        w[14] = (unsigned)(k * 8) | (head ? 1u << 31 : 0u);
         w[15] = (unsigned)(k * stride);
-        for (unsigned v : w) p.ilu64.push_back((int)v);
-      }
+        head = false;
+        w += 16;
+      } while (js);
     }
-    p.ilu64_records = (int)(p.ilu64.size() / 16 + 2) / 3 * 3;
+    const int records = (int)(w - reinterpret_cast<unsigned*>(p.ilu64.data())) / 16;
+    p.ilu64_records = (records + 2) / 3 * 3;
+    p.ilu64.resize((size_t)records * 16);  // the empty ones behind them are zero
     p.ilu64.resize((size_t)(p.ilu64_records + 2) * 16, 0);
   }
 }
@@ -345,6 +373,9 @@ int upload(bs_pattern_s& p) {
     h.resize(std::max(h.size(), off + least), -1);
     return off;
   };
+  h.reserve(p.ilu64.size() + p.seg[0].size() + p.seg[1].size() + p.row_ptr.size() + p.slot_col.size() + 1 +
+            p.row_len.size() + p.diag_slot.size() + p.lev.size() + p.up.size() + p.place.size() +
+            p.ilu_ptr.size() + p.ilu_ops.size() + (p.pos.size() + 1) / 2 + p.layout.size());
   std::vector<int> pos((p.pos.size() + 1) / 2, 0);
   if (!p.pos.empty()) std::memcpy(pos.data(), p.pos.data(), p.pos.size() * sizeof(unsigned short));
   put(p.ilu64);
