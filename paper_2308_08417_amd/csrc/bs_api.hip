@@ -130,9 +130,8 @@ constexpr int kTriRows = 1024;
 // holds (0 if none), its upper level likewise over the columns j > i, taken
 // from the last row up.  Every pattern that a multi-wave shape can take pays
 // for this when it is created, whatever it is used for, so it works on flat
-// arrays of known size (1000 rows of
-// 9 entries, the whole creation: 431 us with a list per row and growing vectors, now
-// 213).
+// arrays of known size (1000 rows of 9 entries, the whole creation: 442 us with a
+// list per row and growing vectors, now 213).
 void tri_schedule(bs_pattern_s& p) {
   const int n = p.n;
   // the strictly lower (0) and upper (1) entries of each row in increasing

@@ -329,10 +329,12 @@ struct Team {
   // Whether any team of this wave satisfies p.  For multi-wave teams every
   // wave sees the same (team-uniform) predicate.
   __device__ __forceinline__ bool any(bool p) const { return wave_any(p); }
-  __device__ __forceinline__ void any2(bool p, bool q, bool& any_p, bool& any_q) const {
-    any_p = wave_any(p);
-    any_q = wave_any(q);
-  }
+  // Two questions in turn, the second asked only after a no to the first: teams
+  // that advance in lockstep (VarTeam) answer both at once and keep the second.
+  // (Both at once here cost the one-row loops up to 3 %: 200 systems of 500 rows, 3
+  // entries each, BiCGSTAB, 339 us, now 333.)
+  __device__ __forceinline__ bool any_first(bool p, bool, bool&) const { return wave_any(p); }
+  __device__ __forceinline__ bool any_second(bool q, bool) const { return wave_any(q); }
   __device__ __forceinline__ unsigned lean_cell(int, int) const { return 0; }
 
 };

@@ -969,9 +969,8 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
         st = ST_MAX_ITER;
       }
     }
-    bool any_chk, any_run;
-    tm.any2(need_chk, st == ST_RUNNING, any_chk, any_run);
-    if (any_chk) {
+    bool any_run;
+    if (tm.any_first(need_chk, st == ST_RUNNING, any_run)) {
       // ---- true residual (plain) / outer refinement step (mixed), FP64
       double t[R], pr[R], q[1];
       kept(kLeanX, P.x);
@@ -1017,7 +1016,7 @@ __device__ __forceinline__ void bicgstab_system(TM& tm, RW& A, const KArgs& g) {
       }
       continue;
     }
-    if (!any_run) break;
+    if (!tm.any_second(st == ST_RUNNING, any_run)) break;
 
     // ---- one BiCGSTAB iteration; committed for teams still running
     bool go = st == ST_RUNNING;
@@ -1313,9 +1312,8 @@ __device__ __forceinline__ void cg_system(TM& tm, RW& A, const KArgs& g) {
       else if (rsq <= lim2) { if (rtrue) st = ST_CONVERGED; else need_chk = true; }
       else if (k >= g.max_iter) st = ST_MAX_ITER;
     }
-    bool any_chk, any_run;
-    tm.any2(need_chk, st == ST_RUNNING, any_chk, any_run);
-    if (any_chk) {
+    bool any_run;
+    if (tm.any_first(need_chk, st == ST_RUNNING, any_run)) {
       double t[R], rc[R], zc[R], p0[R], p1[R], q[2];
       A.template spmv<0>(tm, A.a, P.x, t);
 #pragma unroll
@@ -1343,7 +1341,7 @@ __device__ __forceinline__ void cg_system(TM& tm, RW& A, const KArgs& g) {
       }
       continue;
     }
-    if (!any_run) break;
+    if (!tm.any_second(st == ST_RUNNING, any_run)) break;
     bool go = st == ST_RUNNING;
     if (go && rho == 0.0) { st = ST_BREAKDOWN; go = false; }
     double t[R];

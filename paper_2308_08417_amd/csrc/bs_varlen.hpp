@@ -138,8 +138,9 @@ struct VarTeam {
   // team of one wave does.  Teams in lockstep leave a word per wave and meet
   // at one barrier for both questions.  (8200 systems of 512 to 1024 rows on
   // 512 lanes x 2 rows: 2780 us with a __syncthreads_or for each question, 2140
-  // without; 4100 of 257 to 512 rows, two teams each: 770 and 624 us.)  The sets of words alternate: one is written again
-  // only after the barrier of the other.
+  // without; 4100 of 257 to 512 rows, two teams each: 770 and 624 us.)  The
+  // sets of words alternate: one is written again only after the barrier of the
+  // other.
   __device__ __forceinline__ void any2(bool p, bool q, bool& any_p, bool& any_q) {
     any2_as<false>(p, q, any_p, any_q);
   }
@@ -165,6 +166,12 @@ struct VarTeam {
     any2(p, false, r, unused);
     return r;
   }
+  __device__ __forceinline__ bool any_first(bool p, bool q, bool& any_q) {
+    bool any_p;
+    any2(p, q, any_p, any_q);
+    return any_p;
+  }
+  __device__ __forceinline__ bool any_second(bool, bool any_q) const { return any_q; }
 
   template <class V, int K>
   __device__ __forceinline__ void sum(V (&v)[K]) { sum_as<false>(v); }
@@ -211,6 +218,12 @@ struct ShortTeam : VarTeam<VS> {
     any2(p, false, r, unused);
     return r;
   }
+  __device__ __forceinline__ bool any_first(bool p, bool q, bool& any_q) {
+    bool any_p;
+    any2(p, q, any_p, any_q);
+    return any_p;
+  }
+  __device__ __forceinline__ bool any_second(bool, bool any_q) const { return any_q; }
 };
 
 // The R rows a lane owns, their values and LDS gather addresses in registers.
