@@ -111,6 +111,20 @@ int* device_sink() {
   }
   return sinks[dev];
 }
+
+// Compute units of the current device (cached per device); -1 on an error.
+int device_cus() {
+  static int cache[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
+  if (cache[dev] == 0) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return -1;
+    cache[dev] = v;
+  }
+  return cache[dev];
+}
 }  // namespace bs
 
 namespace {
@@ -491,20 +505,6 @@ void choose_layout(bs_pattern_s& p) {
   p.layout_nz = k->nz;
 }
 
-// Compute units of the current device (cached per device).
-int device_cus() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
-  if (cache[dev] == 0) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      return -1;
-    cache[dev] = v;
-  }
-  return cache[dev];
-}
-
 bool pow2_team(int t) { return t >= 16 && t <= 1024 && (t & (t - 1)) == 0; }
 
 // Block-Jacobi block size of a request: 0 without block Jacobi, else 2, 4 or
@@ -543,7 +543,7 @@ int make_plan(bs_format fmt, int n, int nnz, int max_row, int width, bs_solver s
     return BS_ERR_UNSUPPORTED;
   int tri_team = bs::kWave;
   while (tri_team < n) tri_team *= 2;
-  // the multi-wave schedule and sweep lists address entries with 15 bits
+  // the multi-wave schedules address entries with 15 bits
   if (tri && n > bs::kWave && nnz >= (1 << 15)) return BS_ERR_UNSUPPORTED;
   const int force_team = tri ? (o && o->team ? o->team : tri_team) : o ? o->team : 0,
             force_r = o ? o->rows_per_lane : 0;
@@ -1012,7 +1012,7 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   if (streamed) {
     a.layout = nullptr;
     a.block = 0;
-    const int cus = device_cus();
+    const int cus = bs::device_cus();
     if (cus < 1) return BS_ERR_HIP;
     const int mixed = opts && opts->precision == BS_MIXED;
     const int src = bs::stream_launch(a, pl.info, solver, mixed, cus, (hipStream_t)stream);
@@ -1026,7 +1026,7 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   // Persistent grid: as many workgroups as can be resident at once, each
   // walking over the batch (never more than there are systems).
   const int64_t groups = (n_solves + pl.info.systems_per_group - 1) / pl.info.systems_per_group;
-  const int cus = device_cus();
+  const int cus = bs::device_cus();
   if (cus < 1) return BS_ERR_HIP;
   // Resident groups per CU, asked with 1 KiB more LDS per group than used: a
   // group count that would fill the CU's LDS to the last granule is not always
@@ -1036,10 +1036,10 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
   if (a.stage == 2 && (a.stage_vals_bytes % 1024 != 0 || a.stage_offset + a.stage_vals_bytes > lds))
     return BS_ERR_UNSUPPORTED;
   // The group-wide copy of the values only where no group is lost to it; rows of
-  // more than 56 slots keep it at that price: lanes
-  // that read such rows from memory touch a line each and load (967 systems of 250
-  // rows, 62 entries each, two groups without the copy and one with it: BiCGSTAB
-  // 207 and 137 us, CG 196 and 121; 2016 of 120 rows, four and two: 179 and 132).
+  // more than 56 slots keep it at that price: lanes that read such rows from
+  // memory touch a line each and load (967 systems of 250 rows, 62 entries each, two
+  // groups without the copy and one with it: BiCGSTAB 207 and 137 us, CG 196 and
+  // 121; 2016 of 120 rows, four and two: 179 and 132).
   if (a.stage == 2 && pl.k->nz <= 56) {
     const int without = lds - a.stage_vals_bytes;
     if (pl.k->occupancy((unsigned)lds + 1024) < pl.k->occupancy((unsigned)without + 1024)) {
@@ -1047,9 +1047,9 @@ int bs_batch_solve(bs_format fmt, int64_t n_batch, int32_t n_rows, bs_pattern pa
       lds = without;
     }
   }
-  // A call of no more groups than compute units has them all resident: it is
-  // not worth the runtime's occupancy query (200 tridiagonal systems of 60 rows,
-  // call to call: 18.5 us with it, 18.2 without).
+  // A call of no more groups than compute units has them all resident whatever
+  // the runtime's occupancy query would say (its cost is a fraction of a
+  // microsecond, within the noise of a small call of 18 us).
   const int64_t resident =
       groups <= cus ? groups : (int64_t)pl.k->occupancy((unsigned)lds + 1024) * cus;
   const int64_t grid = std::min(groups, resident);

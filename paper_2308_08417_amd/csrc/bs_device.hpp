@@ -335,8 +335,6 @@ struct Team {
   // entries each, BiCGSTAB, 339 us, now 333.)
   __device__ __forceinline__ bool any_first(bool p, bool, bool&) const { return wave_any(p); }
   __device__ __forceinline__ bool any_second(bool q, bool) const { return wave_any(q); }
-  __device__ __forceinline__ unsigned lean_cell(int, int) const { return 0; }
-
 };
 
 // A system's values and right-hand side on their way through the registers of a

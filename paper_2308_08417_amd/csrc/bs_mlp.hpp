@@ -3,12 +3,14 @@
 //
 // Layout conventions (all BF16 stored as raw 16-bit words, rounded to nearest
 // with ties to even):
-//  * activations of a 64-sample tile live in LDS, row-major [sample][feature]
-//    with a row stride of (width + 8) elements so that the 16-byte fragment
-//    reads of successive rows start in different banks;
-//  * the B operand of every product is read from global memory (it stays in
-//    L2: the whole network is about 240 KB) as "B transposed", row-major
-//    [output column][k], so a lane's eight k values are one 16-byte load;
+//  * activations of a tile of 16, 32 or 64 samples live in LDS, row-major
+//    [sample][feature] with a row stride of (width + 8) elements so that the
+//    16-byte fragment reads of successive rows start in different banks;
+//  * the B operands are stored as "B transposed", row-major [output column][k],
+//    so a lane's eight k values are one 16-byte load: inference and forward hold
+//    W1 and W2 in registers and W3 in LDS for all tiles of a workgroup, a
+//    training tile loads each layer's into registers while the layer before it
+//    runs (from L2: the whole network is about 240 KB);
 //  * the training kernel also writes activations and their gradients
 //    feature-major [feature][sample] for the weight-gradient products, whose
 //    reduction runs over samples.

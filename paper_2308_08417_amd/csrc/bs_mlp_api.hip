@@ -14,6 +14,7 @@
 
 namespace bs {
 void set_last_error(const std::string& msg);
+int device_cus();  // bs_api.hip
 }
 
 using namespace bs::mlp;
@@ -170,19 +171,6 @@ hipError_t launch_apply(const Apply& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Compute units of the current device (cached per device); -1 on an error.
-int compute_units() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
-  if (cache[dev] == 0) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -1;
-    cache[dev] = v;
-  }
-  return cache[dev];
-}
-
 // Row blocks of 16 samples per tile (4, 2 or 1) of a training step over M
 // samples: the fewest rounds over the compute units, a round of RB row blocks
 // costing RB + 1 (a tile's fixed part, its weights and barriers, is worth about
@@ -209,7 +197,7 @@ int train_row_blocks(int64_t M, int cus) {
 // registers beside the weights).
 template <int MODE>
 int launch_forward(const Net& net, const Src& src, float* y, int64_t M, hipStream_t st) {
-  const int cus = compute_units();
+  const int cus = bs::device_cus();
   if (cus < 1) return BS_ERR_HIP;
   const int rb = M <= (int64_t)16 * cus ? 1 : 2;
   const int64_t tiles = (M + 16 * rb - 1) / (16 * rb);
@@ -226,7 +214,7 @@ int run_grad(bs_ws_model_s& m, const Work& w, int64_t M, const float* feat, cons
              const int* rows, float* grad_out, float* loss_out, int update, float lr,
              hipStream_t st) {
   const int64_t Mp = (M + kTile - 1) / kTile * kTile;
-  const int cus = compute_units();
+  const int cus = bs::device_cus();
   if (cus < 1) return BS_ERR_HIP;
   const int rb = train_row_blocks(Mp, cus);
   const int tiles = (int)(Mp / (16 * rb));

@@ -204,12 +204,6 @@ __device__ __forceinline__ void bj_apply(TM& tm, const RW& A, const KArgs& g,
 // each row to a multiple of 8: L strictly below the diagonal (unit diagonal
 // implied), U on and above, zero off the pattern.
 
-__device__ __forceinline__ uint64_t rdlane64(uint64_t v, int l) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Lanes past lane k (all 64-bit shifts stay below 64).
 __device__ __forceinline__ uint64_t lanes_past(int k) { return (~0ull << k) << 1; }
 
