@@ -404,7 +404,8 @@ int bs_varbatch_solve(bs_varbatch vb, const double *values, const double *b, dou
  * candidate, synchronising `stream`) time every single-launch policy, then
  * every class choice for each size class launched alone, then the plan of the
  * best choice per class as a whole; keep the fastest of that plan and the
- * best policy.  One-line report (report may be NULL): "policy=<p or
+ * best policy (of a shape's queue orders the first unless another is 5 % faster:
+ * a few repetitions tell no less apart).  One-line report (report may be NULL): "policy=<p or
  * split:c0,..,c4> times_ms=<t0>,..,<t17> classes=<class>:<code>=<lanes>x<rows>/
  * <walk>/<placement>:<ms>,.. split_ms=<t> key=<key>", '-' for a policy with no
  * kernel for this request.  If cache_path is not NULL the choice is looked up
